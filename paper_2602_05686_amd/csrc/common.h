@@ -179,6 +179,10 @@ class DBuf {
 constexpr int kMaxRuns = 6;
 constexpr int kRunWords = kMaxRuns + 2;
 
+// windows of columns kept per row-dictionary group (see DCsr::drun)
+constexpr int kDictRuns = 8;
+constexpr int kDictRunWords = 2 + 2 * kDictRuns;
+
 // CSR matrix resident on the device
 struct DCsr {
     int n = 0, m = 0;
@@ -194,6 +198,7 @@ struct DCsr {
     DBuf<int> blkk;
     int nblk = 0;
     int group = 1;
+    int max_len = 0;  // longest row
     // packed columns for the streaming SpMV (when every row block's columns
     // span fewer than 2^16 values): col = cbase[b] + col16 within block b
     DBuf<uint16_t> col16;
@@ -212,12 +217,35 @@ struct DCsr {
     // columns keep the runs instead of a list: urun[kRunWords b ..] = {runs,
     // distinct columns, then start | length << 16 per run}; runs = 0: none
     DBuf<uint32_t> urun;
+    // row dictionaries (k_rows.hip), or empty: groups of dk consecutive row
+    // blocks store each distinct row (values and column offsets from the row)
+    // once.  Row r's is drow_of[r] of its group g's rows drow[g] .. drow[g+1],
+    // each start | length << 16 into the group's entries dent[g] .. dent[g+1].
+    // drun[kDictRunWords g ..]: the windows of columns the group gathers from
+    // (number, total length, then first column less the group's first row,
+    // and length, of each, ascending); number 0 where they are not staged.
+    DBuf<uint16_t> drow_of;
+    DBuf<int> drow, dent, doff, drun;
+    DBuf<uint32_t> dinfo;
+    DBuf<double> dval;
+    DBuf<float> dval32;
+    int dk = 0;               // row blocks per group; 0: no dictionaries
+    int64_t dn = 0, de = 0;   // dictionary rows and entries of all groups
+    int dmax_n = 0, dmax_e = 0, dmax_x = 0;  // of the largest group; longest windows
+    int dgroups() const { return dk > 0 ? (nblk + dk - 1) / dk : 0; }
     // the setup kernels' row blocks (at most kStreamCap entries) when the
     // streaming blocks above were widened; otherwise they share blk
     DBuf<int> sblk;
     int snblk = 0;
     const int* setup_blk() const { return sblk ? sblk.get() : blk.get(); }
     int setup_nblk() const { return sblk ? snblk : nblk; }
+    // bytes the streaming kernels read for the matrix, with values of `size`
+    // bytes: the dictionaries and a 16-bit number per row, or values, columns
+    // as stored, row pointer and block tables
+    double stream_bytes(double size) const {
+        if (dk > 0) return 2.0 * n + (size + 4.0) * (double)de + 4.0 * (double)dn + (8.0 + 4.0 * kDictRunWords) * (dgroups() + 1);
+        return (double)nnz * (size + col_bytes()) + 4.0 * (n + 1) + (col16 ? 4.0 * nblk : 0.0) + unique_bytes();
+    }
     // column bytes per stored entry the streaming kernels read
     double col_bytes() const { return col16 ? 2.0 : 4.0; }
     // bytes of the distinct-column lists and their block table
@@ -248,7 +276,17 @@ constexpr int kUniqueReusePct = 70;
 constexpr int kWideBlockMin = 12000;
 constexpr int kWideBlockMinFine = 11000;
 constexpr int kWideBlockMinFp32 = 6000;
+// Row dictionaries are kept when they hold at most a quarter of the stored
+// entries (kDictShare); a group's must fit kDictEntries entries and kDictRows
+// rows of LDS, and its row blocks kDictGroupRows rows.  Windows of more than
+// kDictWindow columns are not staged.
+constexpr int kDictShare = 4;
+constexpr int kDictEntries = 2048;
+constexpr int kDictRows = 512;
+constexpr int kDictWindow = 3072;
+constexpr int kDictMaxBlocks = 6;
 constexpr int kMaxRowsPerBlock = kBlock;
+constexpr int kDictGroupRows = kDictMaxBlocks * kMaxRowsPerBlock;
 constexpr int kLongRow = 96;         // setup kernels: longer single-row blocks take the whole-block path
 constexpr int kWideRow = 32;         // streaming, one thread per row: wider rows are summed by 8 lanes of its wavefront
 // rows longer than this are reduced by a whole block (a block of their own),

@@ -246,12 +246,10 @@ double Hierarchy::time_smoother(int level, int reps, hipStream_t s, double* byte
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     const double sz = fp32 ? 4.0 : 8.0;
-    // val + col (as stored: 4 bytes, or 2 plus a base per block when packed)
-    // + rowptr once, the gathered iterate once, b, D^{-1}, d read, d and x
-    // written
+    // the matrix as stored once, the gathered iterate once, b, D^{-1}, d read,
+    // d and x written
     if (bytes_per_launch)
-        *bytes_per_launch = (double)L.A.nnz * (sz + L.A.col_bytes()) + 4.0 * (L.A.n + 1) +
-                            (L.A.col16 ? 4.0 * L.A.nblk : 0.0) + L.A.unique_bytes() + 6.0 * sz * L.A.n;
+        *bytes_per_launch = L.A.stream_bytes(sz) + 6.0 * sz * L.A.n;
     return ms_total / reps;
 }
 
@@ -412,6 +410,10 @@ void cast_fp32(Hierarchy& h, hipStream_t s) {
         const int nl = L.A.n;
         if (!L.A.val32) L.A.val32.alloc((size_t)(L.A.nnz > 0 ? L.A.nnz : 1), mc);
         cast_vec<double, float>(L.A.nnz, L.A.val.get(), L.A.val32.get(), s);
+        if (L.A.dk > 0) {
+            if (!L.A.dval32) L.A.dval32.alloc((size_t)L.A.de, mc);
+            cast_vec<double, float>(L.A.de, L.A.dval.get(), L.A.dval32.get(), s);
+        }
         if (!L.dinv32) L.dinv32.alloc(nl, mc);
         cast_vec<double, float>(nl, L.dinv.get(), L.dinv32.get(), s);
         if (!L.P.val32) L.P.val32.alloc((size_t)(L.P.nnz > 0 ? L.P.nnz : 1), mc);
@@ -662,6 +664,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
         }
         if (wide_blocks)
             for (int k = 0; k < h.nlev; ++k) widen_stream_blocks(h.lev[k].A, wide_block_min(k, h.fp32), mc, s);
+        row_dictionaries(h.lev[0].A, mc, s);
         smoother_bounds(h, s);
         side.join();
         coarse_inverse_check(h, cflag.get(), s);
@@ -747,11 +750,13 @@ void update_values(Hierarchy& h, const double* val, bool host_ptrs, hipStream_t 
     }
     {
         // as in the setup: the dense coarse inverse beside the smoother bounds
+        // (the new values may repeat rows where the old ones did not, or not)
         coarse_inverse_alloc(h);
         DBuf<double> work((size_t)h.nL * h.nL, mc);
         DBuf<int> cflag(1, mc);
         SideStream side(s);
         coarse_inverse_enqueue(h, work.get(), cflag.get(), side.get());
+        row_dictionaries(h.lev[0].A, mc, s);
         smoother_bounds(h, s);
         side.join();
         coarse_inverse_check(h, cflag.get(), s);
@@ -845,7 +850,7 @@ void Hierarchy::vcycle(const double* r, double* z, DotTarget rz, hipStream_t s) 
 }
 
 // Algorithmic HBM bytes of one V-cycle in the implemented kernel schedule:
-// every streaming SpMV reads val, col and rowptr once and each listed vector
+// every streaming SpMV reads the matrix as stored once and each listed vector
 // once; the coarse GEMV reads the dense inverse.
 double Hierarchy::vcycle_alg_bytes() const {
     const double s = fp32 ? 4.0 : 8.0;
@@ -854,12 +859,7 @@ double Hierarchy::vcycle_alg_bytes() const {
         const Level& L = lev[l];
         const double n = L.A.n, nc = L.nc;
         const double steps = (double)L.c1.size();
-        // a matrix: values, columns as stored for the streaming kernels (4
-        // bytes, or 2 when packed, plus one base per row block), row pointer
-        auto matrix = [&](const DCsr& M) {
-            return (double)M.nnz * (s + M.col_bytes()) + 4.0 * (M.n + 1) + (M.col16 ? 4.0 * M.nblk : 0.0) +
-                   M.unique_bytes();
-        };
+        auto matrix = [&](const DCsr& M) { return M.stream_bytes(s); };
         // smoother SpMVs: (steps-1) pre + steps post; one residual SpMV
         const double n_spmv = (steps - 1.0) + steps + 1.0;
         bytes += n_spmv * matrix(L.A);

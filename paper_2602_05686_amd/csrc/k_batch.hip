@@ -30,6 +30,17 @@ __global__ __launch_bounds__(kBlock) void k_stream_batch(const SArgs<T>* args, c
     stream_block<T, MODE, HAS_DOT, G>(a, gb - starts[j], S);
 }
 
+template <typename T, int MODE, bool HAS_DOT>
+__global__ __launch_bounds__(kBlock) void k_rows_batch(const SArgs<T>* args, const int* starts, int nseg, int total,
+                                                       RowsSize z) {
+    extern __shared__ char lds[];
+    const int gb = xcd_block(total);
+    if (gb >= total) return;
+    const int j = find_segment(starts, nseg, gb);
+    const SArgs<T> a = args[j];
+    rows_group<T, MODE, HAS_DOT>(a, gb - starts[j], z, lds);
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_smooth_first_batch(const SmoothFirstArgs<T>* args, const int* starts,
                                                                int nseg) {
@@ -65,8 +76,13 @@ __global__ __launch_bounds__(kBlock) void k_gemv_batch(const GemvArgs<T>* args, 
 }
 
 template <typename T, int MODE, bool HAS_DOT>
-void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg, int total, hipStream_t s) {
-    if (group == 1)
+void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg, int total, const RowsSize& rs,
+                    hipStream_t s) {
+    if (group == 0) {
+        const RowsSize z = rows_size<T>(rs.max_e, rs.max_n, rs.max_x, HAS_DOT ? kDictGroupRows : 0);
+        hipLaunchKernelGGL((k_rows_batch<T, MODE, HAS_DOT>), dim3(xcd_grid(total)), dim3(kBlock), rows_lds<T>(z).bytes, s,
+                           args, starts, nseg, total, z);
+    } else if (group == 1)
         hipLaunchKernelGGL((k_stream_batch<T, MODE, HAS_DOT, 1>), dim3(xcd_grid(total)), dim3(kBlock), 0, s, args,
                            starts, nseg, total);
     else
@@ -78,23 +94,23 @@ void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg
 
 template <typename T>
 void stream_batch(int mode, bool has_dot, int group, const SArgs<T>* args, const int* starts, int nseg, int total,
-                  hipStream_t s) {
+                  const RowsSize& rs, hipStream_t s) {
     if (nseg <= 0 || total <= 0) return;
-    if (group != 1 && group != 8) fail(AMG_ERR_INVALID_ARG, "batched SpMV: group must be 1 or 8");
+    if (group != 0 && group != 1 && group != 8) fail(AMG_ERR_INVALID_ARG, "batched SpMV: group must be 0, 1 or 8");
     switch (mode) {
-        case M_PLAIN: return stream_batch_t<T, M_PLAIN, false>(group, args, starts, nseg, total, s);
-        case M_RESID: return stream_batch_t<T, M_RESID, false>(group, args, starts, nseg, total, s);
-        case M_ADD: return stream_batch_t<T, M_ADD, false>(group, args, starts, nseg, total, s);
+        case M_PLAIN: return stream_batch_t<T, M_PLAIN, false>(group, args, starts, nseg, total, rs, s);
+        case M_RESID: return stream_batch_t<T, M_RESID, false>(group, args, starts, nseg, total, rs, s);
+        case M_ADD: return stream_batch_t<T, M_ADD, false>(group, args, starts, nseg, total, rs, s);
         case M_SMOOTH:
-            if (has_dot) return stream_batch_t<T, M_SMOOTH, true>(group, args, starts, nseg, total, s);
-            return stream_batch_t<T, M_SMOOTH, false>(group, args, starts, nseg, total, s);
-        case M_DOTPQ: return stream_batch_t<T, M_DOTPQ, true>(group, args, starts, nseg, total, s);
-        case M_RESNORM: return stream_batch_t<T, M_RESNORM, true>(group, args, starts, nseg, total, s);
+            if (has_dot) return stream_batch_t<T, M_SMOOTH, true>(group, args, starts, nseg, total, rs, s);
+            return stream_batch_t<T, M_SMOOTH, false>(group, args, starts, nseg, total, rs, s);
+        case M_DOTPQ: return stream_batch_t<T, M_DOTPQ, true>(group, args, starts, nseg, total, rs, s);
+        case M_RESNORM: return stream_batch_t<T, M_RESNORM, true>(group, args, starts, nseg, total, rs, s);
         default: fail(AMG_ERR_INVALID_ARG, "batched SpMV: unsupported mode");
     }
 }
-template void stream_batch<float>(int, bool, int, const SArgs<float>*, const int*, int, int, hipStream_t);
-template void stream_batch<double>(int, bool, int, const SArgs<double>*, const int*, int, int, hipStream_t);
+template void stream_batch<float>(int, bool, int, const SArgs<float>*, const int*, int, int, const RowsSize&, hipStream_t);
+template void stream_batch<double>(int, bool, int, const SArgs<double>*, const int*, int, int, const RowsSize&, hipStream_t);
 
 template <typename T>
 void smooth_first_batch(const SmoothFirstArgs<T>* args, const int* starts, int nseg, int total, hipStream_t s) {

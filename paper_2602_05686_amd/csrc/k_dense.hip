@@ -9,10 +9,14 @@
 // and the inverse advance together, two launches per diagonal tile: step kb
 // solves the panel below tile kb and block row kb of Y against L_kk, then
 // subtracts both products from the later tiles; the workgroup that updates
-// the next diagonal tile factors it at once, beside the other tiles.  The
-// chain of nt steps bounds the work, not its 4/3 n^3 operations: 4,176
-// unknowns (66 steps) took 16.7 ms as three kernels per factorisation step
-// and two per inverse step with one thread per row of a triangular solve.
+// the next diagonal tile factors it at once, beside the other tiles.  What
+// bounds it is the chain of nt such steps (solve 13 us, update with the next
+// factorisation 25 us) up to about 2,500 unknowns, and beyond that the
+// updates' passes over the two matrices.  Setup of a one-level hierarchy of
+// 1,950 unknowns 6.5 -> 1.7 ms, of 4,225 17.7 -> 4.6 ms, of 4,970 23.5 ->
+// 6.3 ms, against five launches a step with one thread per row of a
+// triangular solve (50 and 36 us), a barrier per column of the diagonal tile
+// (50 us) and products on the vector units.
 //
 // The products run on the FP64 matrix cores (v_mfma_f64_16x16x4: each result
 // is the chain of IEEE fused multiply-adds over ascending k, so a product

@@ -135,10 +135,11 @@ __global__ void k_mark_pow8(int n, const int* jump, int* mark, int* out) {
     }
 }
 
-// out[0] = number of blocks, out[1] = threads per row
+// out[0] = number of blocks, out[1] = threads per row, out[2] = longest row
 __global__ void k_partition_result(int n, const int* pos, const int* par, int* out) {
     out[0] = pos[n];
     out[1] = par[1];
+    out[2] = par[0];
 }
 
 __global__ void k_fill_starts(int n, const int* mark, const int* pos, int* blk) {
@@ -371,6 +372,7 @@ void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap
     A.cap = cap;
     if (n <= 0) {
         A.group = 1;
+        A.max_len = 0;
         A.nblk = 0;
         A.blk.alloc(1, mc);
         A.blkk.alloc(1, mc);
@@ -427,6 +429,7 @@ void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap
     d2h(res, par.get() + 4, 4, s);
     const int nblk = res[0];
     A.group = res[1];
+    A.max_len = res[2];
     A.nblk = nblk;
     A.blk.alloc((size_t)nblk + 1, mc);
     MATAMG_HIP(hipMemcpyAsync(A.blk.get(), blk.get(), sizeof(int) * ((size_t)nblk + 1), hipMemcpyDeviceToDevice, s));

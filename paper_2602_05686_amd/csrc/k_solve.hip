@@ -251,9 +251,21 @@ __global__ __launch_bounds__(kBlock) void k_stream(SArgs<T> a, int nblk) {
 }
 
 template <typename T, int MODE, bool HAS_DOT>
+__global__ __launch_bounds__(kBlock) void k_rows(SArgs<T> a, int groups, RowsSize z) {
+    extern __shared__ char lds[];
+    const int g = xcd_block(groups);
+    if (g >= groups) return;
+    rows_group<T, MODE, HAS_DOT>(a, g, z, lds);
+}
+
+template <typename T, int MODE, bool HAS_DOT>
 void launch_stream(const DCsr& A, const SArgs<T>& a, hipStream_t s) {
     if (A.nblk <= 0) return;
-    if (A.group == 1 && A.cap == kStreamCapWide)
+    if (a.dk > 0) {
+        const RowsSize z = rows_size<T>(A.dmax_e, A.dmax_n, A.dmax_x, HAS_DOT ? a.dk * kMaxRowsPerBlock : 0);
+        hipLaunchKernelGGL((k_rows<T, MODE, HAS_DOT>), dim3(xcd_grid(A.dgroups())), dim3(kBlock), rows_lds<T>(z).bytes,
+                           s, a, A.dgroups(), z);
+    } else if (A.group == 1 && A.cap == kStreamCapWide)
         hipLaunchKernelGGL((k_stream<T, MODE, HAS_DOT, 1, kStreamCapWide>), dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s,
                            a, A.nblk);
     else if (A.group == 1)
@@ -278,6 +290,7 @@ SArgs<T> base_args(const DCsr& A, const T* val, const T* x) {
     a.uoff = A.uoff.get();
     a.urun = A.urun.get();
     a.x = x;
+    dict_args(A, a);
     return a;
 }
 }  // namespace

@@ -34,6 +34,10 @@ void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap
 // the distinct-column lists of A's packed streaming blocks (see DCsr::ustart)
 void block_uniques(DCsr& A, MemCounter* mc, hipStream_t s);
 
+// the row dictionaries of A (see DCsr::drow_of) where its rows repeat; none
+// otherwise.  Synchronises s.
+void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s);
+
 // dot partials of a streaming launch: one per row block
 constexpr int kStreamPartials = 1;  // dot partials per streaming block
 inline int stream_partials(const DCsr& A) { return A.nblk * kStreamPartials; }

@@ -78,6 +78,7 @@ SArgs<T> sargs(const DCsr& M, const T* val, const T* x) {
     a.uoff = M.uoff.get();
     a.urun = M.urun.get();
     a.x = x;
+    dict_args(M, a);
     return a;
 }
 
@@ -89,9 +90,10 @@ struct Stage {
     int kind = K_NONE;
     int mode = 0;
     bool dot = false;
-    std::vector<SArgs<T>> s[2];  // by threads per row: 1, 8
-    std::vector<SArgs<double>> d[2];
-    std::vector<int> sn[2];      // row blocks per record
+    std::vector<SArgs<T>> s[3];  // by threads per row: 1, 8; from row dictionaries
+    std::vector<SArgs<double>> d[3];
+    std::vector<int> sn[3];      // row blocks (dictionary groups) per record
+    RowsSize rs;                 // largest dictionary
     std::vector<SmoothFirstArgs<T>> sf;
     std::vector<GemvArgs<T>> gv;
     std::vector<CgDirArgs> cd;
@@ -99,8 +101,8 @@ struct Stage {
     std::vector<int> vn;         // blocks per record (vector and GEMV stages)
     std::vector<FinishArgs> fin;
     std::vector<std::pair<Request*, DotTarget>> single;
-    size_t off_rec[2] = {0, 0}, off_st[2] = {0, 0};
-    int nseg[2] = {0, 0}, total[2] = {0, 0};
+    size_t off_rec[3] = {0, 0, 0}, off_st[3] = {0, 0, 0};
+    int nseg[3] = {0, 0, 0}, total[3] = {0, 0, 0};
 };
 
 // launch order of a round: down sweep by ascending level, coarsest solve,
@@ -120,25 +122,30 @@ Stage<T>& stage(std::map<int64_t, Stage<T>>& st, int64_t key, int kind, int mode
     return s;
 }
 
+// which of a stage's launches takes a record, with its block count noted
+template <typename S, typename A>
+int stream_slot(S& s, const DCsr& M, const A& a) {
+    if (a.dk <= 0) {
+        const int g = M.group == 1 ? 0 : 1;
+        s.sn[g].push_back(M.nblk);
+        return g;
+    }
+    s.sn[2].push_back(M.dgroups());
+    s.rs.max_e = std::max(s.rs.max_e, M.dmax_e);
+    s.rs.max_n = std::max(s.rs.max_n, M.dmax_n);
+    s.rs.max_x = std::max(s.rs.max_x, M.dmax_x);
+    return 2;
+}
+constexpr int kSlotGroup[3] = {1, 8, 0};
+
 template <typename T>
 void add_stream(Stage<T>& s, const DCsr& M, const SArgs<T>& a) {
-    if (M.nblk <= 0) return;
-    const int g = M.group == 1 ? 0 : 1;
-    s.s[g].push_back(a);
-    s.sn[g].push_back(M.nblk);
+    if (M.nblk > 0) s.s[stream_slot(s, M, a)].push_back(a);
 }
 
-void add_stream64(Stage<float>& s, const DCsr& M, const SArgs<double>& a) {
-    if (M.nblk <= 0) return;
-    const int g = M.group == 1 ? 0 : 1;
-    s.d[g].push_back(a);
-    s.sn[g].push_back(M.nblk);
-}
-void add_stream64(Stage<double>& s, const DCsr& M, const SArgs<double>& a) {
-    if (M.nblk <= 0) return;
-    const int g = M.group == 1 ? 0 : 1;
-    s.d[g].push_back(a);
-    s.sn[g].push_back(M.nblk);
+template <typename T>
+void add_stream64(Stage<T>& s, const DCsr& M, const SArgs<double>& a) {
+    if (M.nblk > 0) s.d[stream_slot(s, M, a)].push_back(a);
 }
 
 // The launches of one V-cycle z = M r of request R, in the order and with
@@ -527,7 +534,7 @@ void Server::run_step(std::vector<Request*>& batch) {
     TableBuilder tb;
     for (auto& kv : st) {
         Stage<T>& s = kv.second;
-        for (int g = 0; g < 2; ++g) {
+        for (int g = 0; g < 3; ++g) {
             if (s.sn[g].empty()) continue;
             s.off_rec[g] = (s.kind == K_STREAM64) ? tb.put(s.d[g]) : tb.put(s.s[g]);
             std::vector<int> pre = prefix(s.sn[g]);
@@ -568,18 +575,18 @@ void Server::run_step(std::vector<Request*>& batch) {
         Stage<T>& s = kv.second;
         switch (s.kind) {
             case K_STREAM:
-                for (int g = 0; g < 2; ++g) {
+                for (int g = 0; g < 3; ++g) {
                     if (!s.nseg[g]) continue;
-                    stream_batch<T>(s.mode, s.dot, g == 0 ? 1 : 8, (const SArgs<T>*)(base + s.off_rec[g]),
-                                    (const int*)(base + s.off_st[g]), s.nseg[g], s.total[g], es_);
+                    stream_batch<T>(s.mode, s.dot, kSlotGroup[g], (const SArgs<T>*)(base + s.off_rec[g]),
+                                    (const int*)(base + s.off_st[g]), s.nseg[g], s.total[g], s.rs, es_);
                     ++launches;
                 }
                 break;
             case K_STREAM64:
-                for (int g = 0; g < 2; ++g) {
+                for (int g = 0; g < 3; ++g) {
                     if (!s.nseg[g]) continue;
-                    stream_batch<double>(s.mode, s.dot, g == 0 ? 1 : 8, (const SArgs<double>*)(base + s.off_rec[g]),
-                                         (const int*)(base + s.off_st[g]), s.nseg[g], s.total[g], es_);
+                    stream_batch<double>(s.mode, s.dot, kSlotGroup[g], (const SArgs<double>*)(base + s.off_rec[g]),
+                                         (const int*)(base + s.off_st[g]), s.nseg[g], s.total[g], s.rs, es_);
                     ++launches;
                 }
                 break;

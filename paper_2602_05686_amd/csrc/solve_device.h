@@ -51,6 +51,16 @@ struct SArgs {
     const double* dotvec;  // SMOOTH: fused dot partner
     T c1, c2;
     DotTarget dt;
+    // row dictionaries (dk > 0: val, col, ... above are not read)
+    int dk, nblk;
+    const uint16_t* drow_of;
+    const int* drow;
+    const int* dent;
+    const uint32_t* dinfo;
+    const int* doff;
+    const int* drun;
+    const T* dval;
+    int n;  // length of the gathered operand
 };
 
 // Per-row operands of the epilogue, loaded before the row's sum is known so
@@ -463,6 +473,190 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         }
     }
 }
+
+// ---------------------------------------------------------- row dictionaries
+// LDS of one group, for the largest of a launch: dictionary values, offsets
+// and row records, the gathered operands' windows, and (dot modes) one term
+// per row
+struct RowsSize {
+    int max_e = 0, max_n = 0, max_x = 0, dots = 0;
+};
+struct RowsLds {
+    int vals, xs, offs, info, bytes;  // byte offsets (the row terms come first), total
+};
+template <typename T>
+__host__ __device__ inline RowsLds rows_lds(const RowsSize& z) {
+    RowsLds l;
+    l.vals = 8 * z.dots;
+    l.xs = l.vals + (int)sizeof(T) * z.max_e;
+    l.offs = l.xs + (int)sizeof(T) * z.max_x;
+    l.info = l.offs + 4 * z.max_e;
+    l.bytes = l.info + 4 * z.max_n;
+    return l;
+}
+// Adds lv[k] x(k) to s over the entries k, k + 1, ... of a row in stored
+// order, C at a time while they last: their operands are loaded together, and
+// each product is rounded before it is added, as the streaming kernel does.
+template <int C, typename T, class X>
+__device__ __forceinline__ void row_chunk(T& s, const T* lv, int& k, int end, X x) {
+#pragma clang fp contract(off)
+    for (; k + C <= end; k += C) {
+        T xv[C];
+#pragma unroll
+        for (int u = 0; u < C; ++u) xv[u] = x(k + u);
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const T p = lv[k + u] * xv[u];
+            s = s + p;
+        }
+    }
+}
+// nine at a time: a third of a 27-point row, all of a 9-point one (more keep
+// fewer wavefronts on a CU: the FP64 fine smoother of the 128^3 stack took
+// 41.5 us with 9, 42.9 with 14 and 51.6 with 27)
+template <typename T, class X>
+__device__ __forceinline__ T row_sum(const T* lv, int k0, int len, X x) {
+    T s = 0;
+    int k = k0;
+    row_chunk<9>(s, lv, k, k0 + len, x);
+    row_chunk<3>(s, lv, k, k0 + len, x);
+    row_chunk<1>(s, lv, k, k0 + len, x);
+    return s;
+}
+
+// Rows of group `g` (dk row blocks) from its dictionary in LDS, one thread
+// per row.  With max_x the operands come from LDS too: the rows of a group
+// gather from a few windows of consecutive columns (three planes of a mesh,
+// say), read once.  A row block's dot terms are summed in the streaming
+// kernel's order (its rows over four wavefronts, each by the wavefront tree,
+// the four sums in order).  What bounds it is the cache path of the gathers:
+// the FP64 fine smoother of the 128^3 stack takes 33 us for the 103 MB of its
+// vectors (staged; 41 us gathering), against 116 us from values and columns,
+// that of the 96^3 cube 25 us (gathering) against 52 us, and the FP32 ones 20
+// and 12 us against 72 and 30 us.
+template <typename T, int MODE, bool HAS_DOT>
+__device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsSize& z, char* lds) {
+    const RowsLds at = rows_lds<T>(z);
+    T* lv = reinterpret_cast<T*>(lds + at.vals);
+    T* xs = reinterpret_cast<T*>(lds + at.xs);
+    int* lo = reinterpret_cast<int*>(lds + at.offs);
+    uint32_t* li = reinterpret_cast<uint32_t*>(lds + at.info);
+    double* ld = reinterpret_cast<double*>(lds);
+    const int b0 = g * a.dk, b1 = min(b0 + a.dk, a.nblk);
+    const int r0 = a.blk[b0], r1 = a.blk[b1];
+    const int m0 = a.drow[g], m1 = a.drow[g + 1], e0 = a.dent[g], e1 = a.dent[g + 1];
+    const int* run = a.drun + (size_t)g * kDictRunWords;
+    const int nrun = z.max_x > 0 ? run[0] : 0, total = run[1];
+    const int first = r0 + (int)threadIdx.x;
+    // the first row's record number and operands travel with the dictionary
+    int id = 0;
+    RowOperands<T> o{};
+    if (first < r1) {
+        id = a.drow_of[first];
+        o = row_operands<T, MODE>(a, first);
+    }
+    if (nrun > 0) {
+        // window j covers the columns first[j] on, at the places end[j - 1] on
+        int shift[kDictRuns], end[kDictRuns];  // column less place
+        int pre = 0;
+#pragma unroll
+        for (int j = 0; j < kDictRuns; ++j) {
+            const bool in = j < nrun;
+            shift[j] = in ? r0 + run[2 + 2 * j] - pre : 0;
+            pre += in ? run[3 + 2 * j] : 0;
+            end[j] = pre;
+        }
+        for (int i = threadIdx.x; i < total; i += kBlock) {
+            int c = shift[0];
+#pragma unroll
+            for (int j = 1; j < kDictRuns; ++j)
+                if (j < nrun && i >= end[j - 1]) c = shift[j];
+            c += i;
+            xs[i] = a.x[min(max(c, 0), a.n - 1)];  // (columns outside the matrix are in no entry)
+        }
+        // an entry's operand for row r0 + i is at place lo + i
+        for (int e = threadIdx.x; e < e1 - e0; e += kBlock) {
+            const int d = a.doff[e0 + e];
+            int c = shift[0];
+#pragma unroll
+            for (int j = 1; j < kDictRuns; ++j)
+                if (j < nrun && d >= run[2 + 2 * j]) c = shift[j];
+            lv[e] = a.dval[e0 + e];
+            lo[e] = r0 + d - c;
+        }
+    } else {
+        for (int e = threadIdx.x; e < e1 - e0; e += kBlock) {
+            lv[e] = a.dval[e0 + e];
+            lo[e] = a.doff[e0 + e];
+        }
+    }
+    for (int m = threadIdx.x; m < m1 - m0; m += kBlock) li[m] = a.dinfo[m0 + m];
+    __syncthreads();
+    for (int r = first; r < r1; r += kBlock) {
+        if (r != first) {
+            id = a.drow_of[r];
+            o = row_operands<T, MODE>(a, r);
+        }
+        const uint32_t w = li[id];
+        const int k0 = (int)(w & 0xffffu), len = (int)(w >> 16);
+        T s;
+        if (nrun > 0) {
+            const T* x = xs + (r - r0);
+            s = row_sum<T>(lv, k0, len, [&](int k) { return x[lo[k]]; });
+        } else {
+            const T* x = a.x + r;
+            s = row_sum<T>(lv, k0, len, [&](int k) { return x[lo[k]]; });
+        }
+        const double dp = epilogue<T, MODE, HAS_DOT>(a, r, s, o);
+        if constexpr (HAS_DOT) ld[r - r0] = dp;
+    }
+    if constexpr (HAS_DOT) {
+        __syncthreads();
+        const int lane = threadIdx.x & 63;
+        for (int b = b0 + (int)(threadIdx.x >> 6); b < b1; b += kBlock / 64) {
+            const int f = a.blk[b], n = a.blk[b + 1] - f;
+            double u = 0.0;
+            for (int w = 0; w < kBlock / 64; ++w) {
+                const int i = 64 * w + lane;
+                const double t = wave_sum(i < n ? ld[f - r0 + i] : 0.0);
+                u = w == 0 ? t : u + t;
+            }
+            if (lane == 0) a.dt.partial[b] = u;
+        }
+    }
+}
+
+// The sizes of M's groups for a launch in precision T.  The windows are
+// staged for FP64 operands where six workgroups' LDS fits a CU: FP32 gathers
+// (half the bytes) and groups with large dictionaries lose more by the lower
+// occupancy and the barrier (FP32 fine smoother of the 128^3 stack 25 us
+// staged, 20 us gathering; FP64 of the 96^3 cube 28 us and 25 us).
+constexpr int kRowsStageLds = 160 * 1024 / 6;
+template <typename T>
+inline RowsSize rows_size(int max_e, int max_n, int max_x, int dots) {
+    RowsSize z{max_e, max_n, max_x, dots};
+    if (sizeof(T) == 4 || rows_lds<T>(RowsSize{max_e, max_n, max_x, 0}).bytes > kRowsStageLds) z.max_x = 0;
+    return z;
+}
+
+// the dictionary of M as the arguments of a streaming launch, if M has one in
+// this precision
+template <typename T>
+inline void dict_args(const DCsr& M, const T* dval, SArgs<T>& a) {
+    if (M.dk <= 0 || !dval) return;
+    a.dk = M.dk;
+    a.nblk = M.nblk;
+    a.n = M.m;
+    a.drow_of = M.drow_of.get();
+    a.drow = M.drow.get();
+    a.dent = M.dent.get();
+    a.dinfo = M.dinfo.get();
+    a.doff = M.doff.get();
+    a.drun = M.drun.get();
+    a.dval = dval;
+}
+inline void dict_args(const DCsr& M, SArgs<double>& a) { dict_args<double>(M, M.dval.get(), a); }
+inline void dict_args(const DCsr& M, SArgs<float>& a) { dict_args<float>(M, M.dval32.get(), a); }
 
 // ------------------------------------------------------------ vector bodies
 // Grid-stride loops over one problem's vectors: block `lb` of `grid`.
