@@ -10,6 +10,9 @@
 
 namespace matamg {
 
+// device scalar slots
+enum Scalar { S_RZ0 = 0, S_RZ1 = 1, S_PQ = 2, S_RR = 3, S_BB = 4, S_TMP = 5, S_NSCAL = 8 };
+
 struct Level {
     DCsr A, P, R;  // operator; prolongator to / restriction from the next level
     DBuf<double> dinv;
@@ -36,9 +39,12 @@ struct Hierarchy {
     MemCounter mem;
     DBuf<double> scal;       // device scalars (see Scalar)
     DBuf<double> partial;    // reduction partials
-    DBuf<unsigned> counter;  // reduction counters
+    DBuf<double> partial2;   // a solve's r.r partials (beside p.q's, which the same kernel reads)
+    DBuf<unsigned> counter;  // reduction counters; [1]: the reported steps of the solves
     DBuf<double> cr, cz, cp, cq, cx, cb;  // CG vectors (x, b used for host inputs)
-    double* hscal = nullptr; // pinned host mirror of scal
+    double* hscal = nullptr; // pinned host mirror of scal, and behind it the step it holds
+    unsigned* hstep() const { return reinterpret_cast<unsigned*>(hscal + S_NSCAL); }
+    unsigned steps = 0;      // steps asked to report so far
     hipStream_t ws = nullptr;        // the solve's own stream (graphs cannot capture the null stream)
     hipEvent_t ev_in = nullptr;      // orders the solve after the caller's stream
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // captured CG steps, by parity
@@ -49,18 +55,19 @@ struct Hierarchy {
 
     ~Hierarchy();
     DotTarget dt(int slot) const;
-    void vcycle(const double* r, double* z, DotTarget rz, hipStream_t s);
+    // first_done: the finest level's first smoother step has been taken
+    void vcycle(const double* r, double* z, DotTarget rz, hipStream_t s, bool first_done = false);
     template <typename T>
-    void vcycle_t(const double* r, double* z, DotTarget rz, hipStream_t s);
+    void vcycle_t(const double* r, double* z, DotTarget rz, hipStream_t s, bool first_done);
+    template <typename T>
+    FirstStep<T> first_step();
     double vcycle_alg_bytes() const;
     double time_smoother(int level, int reps, hipStream_t s, double* bytes_per_launch);
-    hipGraphExec_t step_graph(int cur);
+    hipGraphExec_t step_graph(const struct PcgWork& w, int cur);
+    void first_smooth(const double* r, hipStream_t s);
     void ensure_solve_resources();
     void release_setup_data();
 };
-
-// device scalar slots
-enum Scalar { S_RZ0 = 0, S_RZ1 = 1, S_PQ = 2, S_RR = 3, S_BB = 4, S_TMP = 5, S_NSCAL = 8 };
 
 // wide_blocks: give large finest-level operators the wider streaming blocks
 // (the batched launches of the server take only kStreamCap blocks)
@@ -81,7 +88,9 @@ amg_status pcg_solve(Hierarchy& h, const double* b, double* x, double tol, int m
 // (device vectors of the finest size), the device scalars (S_NSCAL), the
 // reduction partials and counter, a host mirror of the scalars, the stream,
 // and whether the captured step graphs may run (only with the hierarchy's
-// own buffers, which they hold).
+// own buffers, which they hold).  With partial2 the steps leave short sums to
+// the kernels that need them, take the next V-cycle's first smoother step and
+// report their scalars into the hierarchy's pinned memory.
 struct PcgWork {
     double *x, *r, *z, *p, *q;
     double* scal;
@@ -90,6 +99,7 @@ struct PcgWork {
     double* hscal;
     hipStream_t stream;
     bool graphs;
+    double* partial2;
 };
 // the PCG iteration of pcg_solve on a given workspace; allocates nothing
 amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, int max_iter, int* iters,

@@ -256,7 +256,10 @@ double Hierarchy::time_smoother(int level, int reps, hipStream_t s, double* byte
 // the solve's own stream, ordering event and pinned scalar mirror, created
 // on the first solve (hierarchies driven by the solve server never need them)
 void Hierarchy::ensure_solve_resources() {
-    if (!hscal) MATAMG_HIP(hipHostMalloc((void**)&hscal, sizeof(double) * S_NSCAL, hipHostMallocDefault));
+    if (!hscal) {
+        MATAMG_HIP(hipHostMalloc((void**)&hscal, sizeof(double) * (S_NSCAL + 1), hipHostMallocDefault));
+        *hstep() = steps;
+    }
     if (!ws) ws = take_stream();
     if (!ev_in) MATAMG_HIP(hipEventCreateWithFlags(&ev_in, hipEventDisableTiming));
 }
@@ -475,8 +478,8 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
     MemCounter* mc = &h.mem;
 
     h.scal.alloc(S_NSCAL, mc);
-    h.counter.alloc(1, mc);
-    zero_async(h.counter.get(), sizeof(unsigned), s);
+    h.counter.alloc(2, mc);
+    zero_async(h.counter.get(), 2 * sizeof(unsigned), s);
     zero_async(h.scal.get(), sizeof(double) * S_NSCAL, s);
     {
         // MATAMG_NO_GRAPH=1 runs every CG step eagerly (used to check the
@@ -685,6 +688,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
     h.cz.alloc(n0, mc);
     h.cp.alloc(n0, mc);
     h.cq.alloc(n0, mc);
+    h.partial2.alloc((size_t)vector_partials((int64_t)n0), mc);
     MATAMG_HIP(hipStreamSynchronize(s));
     h.t_setup = now_s() - t0;
     return hp;
@@ -773,7 +777,14 @@ void update_values(Hierarchy& h, const double* val, bool host_ptrs, hipStream_t 
 }
 
 template <typename T>
-void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream_t s) {
+FirstStep<T> Hierarchy::first_step() {
+    using V = Vec<T>;
+    Level& L = lev[0];
+    return FirstStep<T>{std::is_same<T, double>::value ? nullptr : V::b(L), V::dinv(L), (T)L.c2[0], V::d(L), V::xa(L)};
+}
+
+template <typename T>
+void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream_t s, bool first_done) {
     using V = Vec<T>;
     const int L = nlev;
     if (L == 1) {
@@ -798,7 +809,7 @@ void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream
         T* y = V::xb(Lv);
         // the first step from zero; below the finest level the restriction
         // that made b has already taken it
-        if (l == 0) smooth_first<T>(n, b64, b, V::dinv(Lv), (T)Lv.c2[0], V::d(Lv), x, s);
+        if (l == 0 && !first_done) smooth_first<T>(n, b64, b, V::dinv(Lv), (T)Lv.c2[0], V::d(Lv), x, s);
         for (size_t k = 1; k < Lv.c1.size(); ++k) {
             spmv_smooth<T>(Lv.A, V::A(Lv.A), x, b, V::dinv(Lv), V::d(Lv), (T)Lv.c1[k], (T)Lv.c2[k], y, nullptr,
                            nullptr, DotTarget{}, s);
@@ -844,9 +855,24 @@ void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream
     }
 }
 
-void Hierarchy::vcycle(const double* r, double* z, DotTarget rz, hipStream_t s) {
-    if (fp32) vcycle_t<float>(r, z, rz, s);
-    else vcycle_t<double>(r, z, rz, s);
+// the finest level's first smoother step from r, as the V-cycle takes it
+void Hierarchy::first_smooth(const double* r, hipStream_t s) {
+    const int n = lev[0].A.n;
+    auto run = [&](auto tag) {
+        using T = decltype(tag);
+        const FirstStep<T> f = first_step<T>();
+        if constexpr (std::is_same<T, double>::value)
+            smooth_first<double>(n, nullptr, const_cast<double*>(r), f.dinv, f.c2, f.d, f.x, s);
+        else
+            smooth_first<float>(n, r, f.b, f.dinv, f.c2, f.d, f.x, s);
+    };
+    if (fp32) run(float{});
+    else run(double{});
+}
+
+void Hierarchy::vcycle(const double* r, double* z, DotTarget rz, hipStream_t s, bool first_done) {
+    if (fp32) vcycle_t<float>(r, z, rz, s, first_done);
+    else vcycle_t<double>(r, z, rz, s, first_done);
 }
 
 // Algorithmic HBM bytes of one V-cycle in the implemented kernel schedule:
@@ -879,22 +905,68 @@ double Hierarchy::vcycle_alg_bytes() const {
 }
 
 // ---------------------------------------------------------------------- PCG
-// One captured graph per parity of the iteration counter: the V-cycle and
-// search-direction update of step k followed by q = A p and the x / r update
-// of step k + 1.  All operands are hierarchy-owned buffers, so the two
-// graphs are captured once per hierarchy and replayed every step; the
-// convergence test reads the device scalars after each replay.
-hipGraphExec_t Hierarchy::step_graph(int cur) {
+namespace {
+
+// One CG step: z = M r, p = z + beta p (old < 0: p = z), q = A p, and x, r
+// updated, with the scalars in slots nxt (this step's r.z) and old.
+// first_done: the step before has taken the V-cycle's first smoother step.
+void cg_step(Hierarchy& h, const PcgWork& w, int nxt, int old, bool first_done) {
+    const DCsr& A = h.lev[0].A;
+    const int n = A.n;
+    hipStream_t s = w.stream;
+    auto dt = [&](int slot) { return DotTarget{w.partial, w.counter, w.scal + slot}; };
+    const int nb = stream_partials(A);
+    const bool own = w.partial2 && h.nlev > 1 && nb <= kOwnSumPartials;
+    const DotTarget left{w.partial, w.counter, nullptr};
+    h.vcycle(w.r, w.z, own ? left : dt(nxt), s, first_done);
+    cg_direction(n, w.p, w.z, w.scal + nxt, old >= 0 ? w.scal + old : nullptr, own ? left : DotTarget{}, nb, s);
+    spmv_dot(A, w.p, w.q, own ? left : dt(S_PQ), s);
+    auto update = [&](auto tag) {
+        using T = decltype(tag);
+        FirstStep<T> f{};
+        if (h.nlev > 1) f = h.first_step<T>();
+        DotTarget rr = dt(S_RR);
+        if (w.partial2) rr = DotTarget{w.partial2, w.counter, nullptr};
+        cg_update<T>(n, w.x, w.r, w.p, w.q, w.scal + nxt, w.scal + S_PQ, own ? left : DotTarget{}, nb, rr,
+                     w.partial2 && h.nlev > 1 ? &f : nullptr, s);
+    };
+    if (h.fp32) update(float{});
+    else update(double{});
+    if (w.partial2)
+        finish_report(DotTarget{w.partial2, w.counter, w.scal + S_RR}, vector_partials(n), w.scal, S_NSCAL,
+                      h.counter.get() + 1, h.hscal, h.hstep(), s);
+}
+
+// Waits for the last step asked to report.  The scalars arrive in pinned
+// memory a few microseconds before a copy and a stream synchronisation would
+// bring them, which small systems' steps would wait out each time.
+void wait_report(Hierarchy& h, hipStream_t s) {
+    for (unsigned spin = 1;; ++spin) {
+        if ((int)(__atomic_load_n(h.hstep(), __ATOMIC_ACQUIRE) - h.steps) >= 0) return;
+        if (spin % 4096 == 0) {
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess) (void)hipGetLastError();
+            MATAMG_HIP(e);
+            // the stream is idle: the step has reported, or never will
+            if ((int)(__atomic_load_n(h.hstep(), __ATOMIC_ACQUIRE) - h.steps) >= 0) return;
+            fail(AMG_ERR_HIP, "a CG step ended without reporting its scalars");
+        }
+    }
+}
+
+}  // namespace
+
+// One captured graph per parity of the iteration counter: one CG step.  All
+// operands are hierarchy-owned buffers, so the two graphs are captured once
+// per hierarchy and replayed every step; the convergence test reads the
+// scalars after each replay.
+hipGraphExec_t Hierarchy::step_graph(const PcgWork& w, int cur) {
     const int g = (cur == S_RZ0) ? 0 : 1;
     if (graph[g]) return graph[g];
     const int nxt = (cur == S_RZ0) ? S_RZ1 : S_RZ0;
-    const DCsr& A = lev[0].A;
-    const int n = A.n;
     MATAMG_HIP(hipStreamBeginCapture(ws, hipStreamCaptureModeThreadLocal));
-    vcycle(cr.get(), cz.get(), dt(nxt), ws);
-    cg_direction(n, cp.get(), cz.get(), scal.get() + nxt, scal.get() + cur, ws);
-    spmv_dot(A, cp.get(), cq.get(), dt(S_PQ), ws);
-    cg_update(n, cx.get(), cr.get(), cp.get(), cq.get(), scal.get() + nxt, scal.get() + S_PQ, dt(S_RR), ws);
+    cg_step(*this, w, nxt, cur, nlev > 1);
     hipGraph_t gr = nullptr;
     MATAMG_HIP(hipStreamEndCapture(ws, &gr));
     hipGraphExec_t ex = nullptr;
@@ -921,8 +993,6 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
     hipStream_t ws = w.stream;
     double* x = w.x;
     double* r = w.r;
-    double* z = w.z;
-    double* p = w.p;
     double* q = w.q;
     auto dt = [&](int slot) { return DotTarget{w.partial, w.counter, w.scal + slot}; };
     auto read_scal = [&]() {
@@ -948,12 +1018,12 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
     } else if (max_iter > 0) {
         // first step eagerly: z = M r, p = z, q = A p, x and r updated
         int cur = S_RZ0;
-        h.vcycle(r, z, dt(cur), ws);
-        cg_direction(n, p, z, w.scal + cur, nullptr, ws);
-        spmv_dot(A, p, q, dt(S_PQ), ws);
-        cg_update(n, x, r, p, q, w.scal + cur, w.scal + S_PQ, dt(S_RR), ws);
+        const bool fused = w.partial2 && h.nlev > 1;  // a step takes the next one's first smoother step
+        cg_step(h, w, cur, -1, false);
+        if (w.partial2) ++h.steps;
         for (int it = 1;; ++it) {
-            read_scal();
+            if (w.partial2) wait_report(h, ws);
+            else read_scal();
             iters = it;
             const double pq = w.hscal[S_PQ], rzv = w.hscal[cur];
             if (!(pq > 0.0) || !std::isfinite(pq) || !std::isfinite(rzv)) {
@@ -970,19 +1040,15 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
                     st = AMG_OK;
                     break;
                 }
-                // residual replacement
+                // residual replacement, and the first smoother step from it
                 MATAMG_HIP(hipMemcpyAsync(r, q, sizeof(double) * n, hipMemcpyDeviceToDevice, ws));
+                if (fused && it < max_iter) h.first_smooth(r, ws);
             }
             if (it >= max_iter) break;
             const int nxt = (cur == S_RZ0) ? S_RZ1 : S_RZ0;
-            if (w.graphs) {
-                MATAMG_HIP(hipGraphLaunch(h.step_graph(cur), ws));
-            } else {
-                h.vcycle(r, z, dt(nxt), ws);
-                cg_direction(n, p, z, w.scal + nxt, w.scal + cur, ws);
-                spmv_dot(A, p, q, dt(S_PQ), ws);
-                cg_update(n, x, r, p, q, w.scal + nxt, w.scal + S_PQ, dt(S_RR), ws);
-            }
+            if (w.graphs) MATAMG_HIP(hipGraphLaunch(h.step_graph(w, cur), ws));
+            else cg_step(h, w, nxt, cur, fused);
+            if (w.partial2) ++h.steps;
             cur = nxt;
         }
     }
@@ -996,6 +1062,7 @@ amg_status pcg_solve(Hierarchy& h, const double* b_in, double* x_io, double tol,
     const double t0 = now_s();
     const int n = h.lev[0].A.n;
     h.ensure_solve_resources();
+    h.steps = __atomic_load_n(h.hstep(), __ATOMIC_ACQUIRE);  // (the stream is idle between solves)
     hipStream_t ws = h.ws;
     // order after the caller's earlier work on its stream
     MATAMG_HIP(hipEventRecord(h.ev_in, s));
@@ -1012,7 +1079,7 @@ amg_status pcg_solve(Hierarchy& h, const double* b_in, double* x_io, double tol,
     }
     // the captured step graphs hold these buffers
     PcgWork w{x, h.cr.get(), h.cz.get(), h.cp.get(), h.cq.get(), h.scal.get(), h.partial.get(), h.counter.get(),
-              h.hscal, ws, h.use_graphs};
+              h.hscal, ws, h.use_graphs, h.partial2.get()};
     int iters = 0;
     double rel_true = 0.0;
     const amg_status st = pcg_run(h, w, b, tol, max_iter, &iters, &rel_true);

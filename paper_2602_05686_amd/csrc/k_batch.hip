@@ -52,14 +52,14 @@ __global__ __launch_bounds__(kBlock) void k_smooth_first_batch(const SmoothFirst
 __global__ __launch_bounds__(kBlock) void k_cg_direction_batch(const CgDirArgs* args, const int* starts, int nseg) {
     const int j = find_segment(starts, nseg, blockIdx.x);
     const CgDirArgs a = args[j];
-    cg_direction_body(a, blockIdx.x - starts[j], starts[j + 1] - starts[j]);
+    cg_direction_body(a, blockIdx.x - starts[j], starts[j + 1] - starts[j], nullptr);  // (its sums have their own launch)
 }
 
 __global__ __launch_bounds__(kBlock) void k_cg_update_batch(const CgUpdArgs* args, const int* starts, int nseg) {
     __shared__ double sh[kBlock / 64];
     const int j = find_segment(starts, nseg, blockIdx.x);
     const CgUpdArgs a = args[j];
-    cg_update_body(a, blockIdx.x - starts[j], starts[j + 1] - starts[j], sh);
+    cg_update_body<double>(a, nullptr, blockIdx.x - starts[j], starts[j + 1] - starts[j], sh);
 }
 
 __global__ __launch_bounds__(kFinishThreads) void k_finish_batch(const FinishArgs* args) {

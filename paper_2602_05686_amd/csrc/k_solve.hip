@@ -273,7 +273,7 @@ void launch_stream(const DCsr& A, const SArgs<T>& a, hipStream_t s) {
     else
         hipLaunchKernelGGL((k_stream<T, MODE, HAS_DOT, 8>), dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s, a, A.nblk);
     MATAMG_LAUNCH_CHECK();
-    if constexpr (HAS_DOT) finish_sum(a.dt, stream_partials(A), s);
+    if (HAS_DOT && a.dt.result) finish_sum(a.dt, stream_partials(A), s);
 }
 
 template <typename T>
@@ -398,13 +398,29 @@ __global__ __launch_bounds__(kBlock) void k_scale_inv_norm(int64_t n, const doub
         out[i] = in[i] * inv;
 }
 
-__global__ __launch_bounds__(kBlock) void k_cg_update(CgUpdArgs a) {
-    __shared__ double sh[kBlock / 64];
-    cg_update_body(a, blockIdx.x, gridDim.x, sh);
+template <typename T, bool FIRST>
+__global__ __launch_bounds__(kBlock) void k_cg_update(CgUpdArgs a, SmoothFirstArgs<T> first) {
+    __shared__ double sh[kFinishWaves];
+    cg_update_body<T>(a, FIRST ? &first : nullptr, blockIdx.x, gridDim.x, sh);
 }
 
 __global__ __launch_bounds__(kBlock) void k_cg_direction(CgDirArgs a) {
-    cg_direction_body(a, blockIdx.x, gridDim.x);
+    __shared__ double sh[kFinishWaves];
+    cg_direction_body(a, blockIdx.x, gridDim.x, sh);
+}
+
+// finish_body, and then the solve's scalars to the host's copy (pinned
+// memory), its step number last
+__global__ __launch_bounds__(kFinishThreads) void k_finish_report(FinishArgs a, const double* scal, int words,
+                                                                  unsigned* step, double* host, unsigned* host_step) {
+    __shared__ double sh[kFinishThreads / 64];
+    finish_body(a, sh);
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < words; ++k) host[k] = scal[k];
+        const unsigned s = *step + 1u;
+        *step = s;
+        __hip_atomic_store(host_step, s, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 template <typename A, typename B>
@@ -447,18 +463,39 @@ void scale_by_inv_norm(int64_t n, const double* nrm2, const double* in, double* 
     MATAMG_LAUNCH_CHECK();
 }
 
-void cg_update(int64_t n, double* x, double* r, const double* p, const double* q, const double* rz,
-               const double* pq, DotTarget rr, hipStream_t s) {
+template <typename T>
+void cg_update(int64_t n, double* x, double* r, const double* p, const double* q, const double* rz, double* pq,
+               DotTarget pqs, int pq_blocks, DotTarget rr, const FirstStep<T>* first, hipStream_t s) {
     const int g = vec_grid(n);
-    hipLaunchKernelGGL(k_cg_update, dim3(g), dim3(kBlock), 0, s, CgUpdArgs{n, x, r, p, q, rz, pq, rr.partial});
+    const CgUpdArgs a{n, x, r, p, q, rz, pq, rr.partial, pqs.partial, pq_blocks};
+    if (first)
+        hipLaunchKernelGGL((k_cg_update<T, true>), dim3(g), dim3(kBlock), 0, s, a,
+                           SmoothFirstArgs<T>{n, first->b ? r : nullptr, first->b, first->dinv, first->c2, first->d,
+                                              first->x});
+    else
+        hipLaunchKernelGGL((k_cg_update<T, false>), dim3(g), dim3(kBlock), 0, s, a, SmoothFirstArgs<T>{});
     MATAMG_LAUNCH_CHECK();
-    finish_sum(rr, g, s);
+    if (rr.result) finish_sum(rr, g, s);
+}
+template void cg_update<double>(int64_t, double*, double*, const double*, const double*, const double*, double*,
+                                DotTarget, int, DotTarget, const FirstStep<double>*, hipStream_t);
+template void cg_update<float>(int64_t, double*, double*, const double*, const double*, const double*, double*,
+                               DotTarget, int, DotTarget, const FirstStep<float>*, hipStream_t);
+
+void cg_direction(int64_t n, double* p, const double* z, double* rz_new, const double* rz_old, DotTarget rzs,
+                  int rz_blocks, hipStream_t s) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_cg_direction, dim3(vec_grid(n)), dim3(kBlock), 0, s,
+                       CgDirArgs{n, p, z, rz_new, rz_old, rzs.partial, rz_blocks});
+    MATAMG_LAUNCH_CHECK();
 }
 
-void cg_direction(int64_t n, double* p, const double* z, const double* rz_new, const double* rz_old,
-                  hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_cg_direction, dim3(vec_grid(n)), dim3(kBlock), 0, s, CgDirArgs{n, p, z, rz_new, rz_old});
+int vector_partials(int64_t n) { return vec_grid(n); }
+
+void finish_report(const DotTarget& dt, int nblocks, const double* scal, int words, unsigned* step, double* host,
+                   unsigned* host_step, hipStream_t s) {
+    hipLaunchKernelGGL(k_finish_report, dim3(1), dim3(kFinishThreads), 0, s,
+                       FinishArgs{nblocks, dt.partial, dt.result}, scal, words, step, host, host_step);
     MATAMG_LAUNCH_CHECK();
 }
 

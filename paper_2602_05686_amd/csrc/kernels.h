@@ -42,7 +42,8 @@ void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s);
 constexpr int kStreamPartials = 1;  // dot partials per streaming block
 inline int stream_partials(const DCsr& A) { return A.nblk * kStreamPartials; }
 
-// dot-fusion target: per-block partial sums, reduced by finish_sum into *result
+// dot-fusion target: per-block partial sums, reduced by finish_sum into
+// *result (result null: left to the kernel that needs the sum)
 struct DotTarget {
     double* partial = nullptr;
     unsigned* counter = nullptr;
@@ -86,12 +87,34 @@ template <typename T>
 void smooth_first(int64_t n, const double* b64, T* b, const T* dinv, T c2, T* d, T* x, hipStream_t s);
 // v = v / sqrt(*nrm2)
 void scale_by_inv_norm(int64_t n, const double* nrm2, const double* in, double* out, hipStream_t s);
-// CG: alpha = rz/pq; x += alpha p; r -= alpha q; rr = r.r
-void cg_update(int64_t n, double* x, double* r, const double* p, const double* q, const double* rz,
-               const double* pq, DotTarget rr, hipStream_t s);
-// CG: p = z + (rz_new / rz_old) p  (rz_old == nullptr: p = z)
-void cg_direction(int64_t n, double* p, const double* z, const double* rz_new, const double* rz_old,
-                  hipStream_t s);
+// most partials that a kernel which needs their sum adds up itself
+constexpr int kOwnSumPartials = 1024;
+// the finest level's first smoother step from zero, as smooth_first takes it
+// (b null: the right-hand side is r itself)
+template <typename T>
+struct FirstStep {
+    T* b;
+    const T* dinv;
+    T c2;
+    T* d;
+    T* x;
+};
+// CG: alpha = rz/pq; x += alpha p; r -= alpha q; rr = r.r (its partials,
+// vector_partials(n) of them, are left if rr.result is null).  pqs.partial,
+// if set, holds pq as pq_blocks partials, and pq is stored.  first (or null):
+// also the next V-cycle's first smoother step, from the new r.
+template <typename T>
+void cg_update(int64_t n, double* x, double* r, const double* p, const double* q, const double* rz, double* pq,
+               DotTarget pqs, int pq_blocks, DotTarget rr, const FirstStep<T>* first, hipStream_t s);
+// CG: p = z + (rz_new / rz_old) p  (rz_old == nullptr: p = z); rzs.partial, if
+// set, holds rz_new as rz_blocks partials, and rz_new is stored
+void cg_direction(int64_t n, double* p, const double* z, double* rz_new, const double* rz_old, DotTarget rzs,
+                  int rz_blocks, hipStream_t s);
+int vector_partials(int64_t n);
+// finish_sum, then `words` of scal to host memory (pinned), then *step + 1 to
+// *step and *host_step
+void finish_report(const DotTarget& dt, int nblocks, const double* scal, int words, unsigned* step, double* host,
+                   unsigned* host_step, hipStream_t s);
 template <typename A, typename B>
 void cast_vec(int64_t n, const A* in, B* out, hipStream_t s);
 void fill_seeded_uniform(int64_t n, uint64_t key, double* v, hipStream_t s);

@@ -79,7 +79,7 @@ amg_status pcg_solve_noalloc(Hierarchy& h, const double* b, double* x, double to
     zero_async(scal, sizeof(double) * S_NSCAL, s);
     zero_async(counter, sizeof(unsigned), s);
     double hscal[S_NSCAL] = {};
-    PcgWork w{x, r, z, p, q, scal, partial, counter, hscal, s, false};
+    PcgWork w{x, r, z, p, q, scal, partial, counter, hscal, s, false, nullptr};
     int iters = 0;
     double rel_true = 0.0;
     const amg_status st = pcg_run(h, w, b, tol, max_iter, &iters, &rel_true);

@@ -511,7 +511,7 @@ void Server::run_step(std::vector<Request*>& batch) {
         emit_vcycle<T>(st, R, rz);
         {
             Stage<T>& s = stage<T>(st, key_cg(0), K_CGDIR);
-            s.cd.push_back(CgDirArgs{n, h.cp.get(), h.cz.get(), sc + target, R->first ? nullptr : sc + R->cur});
+            s.cd.push_back(CgDirArgs{n, h.cp.get(), h.cz.get(), sc + target, R->first ? nullptr : sc + R->cur, nullptr, 0});
             s.vn.push_back(vec_grid(n));
         }
         {
@@ -524,7 +524,7 @@ void Server::run_step(std::vector<Request*>& batch) {
         {
             Stage<T>& s = stage<T>(st, key_cg(3), K_CGUPD);
             s.cu.push_back(CgUpdArgs{n, h.cx.get(), h.cr.get(), h.cp.get(), h.cq.get(), sc + target, sc + S_PQ,
-                                     h.partial.get()});
+                                     h.partial.get(), nullptr, 0});
             s.vn.push_back(vec_grid(n));
         }
         stage<T>(st, key_cg(4), K_FINISH).fin.push_back(FinishArgs{vec_grid(n), h.partial.get(), sc + S_RR});

@@ -688,16 +688,54 @@ __device__ __forceinline__ void smooth_first_body(const SmoothFirstArgs<T>& a, i
     }
 }
 
+// *result = sum of partial[0..nb) (one block of kFinishThreads threads).
+// Thread t adds partial[t], partial[t + T], ... in ascending order, four
+// independent loads in flight at a time; the per-thread sums are combined
+// by a fixed tree.  The order depends on nb only.
+constexpr int kFinishThreads = 1024;
+constexpr int kFinishWaves = kFinishThreads / 64;
+
+// The same sum of at most kFinishThreads partials, by a block of kBlock
+// threads, on every thread: a kernel that needs a sum of few partials takes
+// it itself, in each of its blocks, instead of waiting for a launch of its
+// own (3 to 4 us, of about 100 us a CG step on small systems).  sh:
+// kFinishWaves doubles.
+__device__ __forceinline__ double finish_block(const double* partial, int nb, double* sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < kFinishThreads / kBlock; ++j) {
+        const int t = (int)threadIdx.x + j * kBlock;
+        double v = 0.0;
+        if (t < nb) v += partial[t];
+        v = wave_sum(v);
+        if (lane == 0) sh[w + j * (kBlock / 64)] = v;
+    }
+    __syncthreads();
+    double t = sh[0];
+    for (int k = 1; k < kFinishWaves; ++k) t += sh[k];
+    __syncthreads();
+    return t;
+}
+
 struct CgDirArgs {
     int64_t n;
     double* p;
     const double* z;
-    const double* rz_new;
+    double* rz_new;
     const double* rz_old;  // null: p = z
+    const double* part;    // if set: rz_new is the sum of part[0..npart), stored here
+    int npart;
 };
 
-__device__ __forceinline__ void cg_direction_body(const CgDirArgs& a, int lb, int grid) {
-    const double beta = a.rz_old ? (*a.rz_new / *a.rz_old) : 0.0;
+__device__ __forceinline__ void cg_direction_body(const CgDirArgs& a, int lb, int grid, double* sh) {
+    double rz = 0.0;
+    if (a.part) {
+        rz = finish_block(a.part, a.npart, sh);
+        if (lb == 0 && threadIdx.x == 0) *a.rz_new = rz;
+    } else if (a.rz_old) {
+        rz = *a.rz_new;
+    }
+    const double beta = a.rz_old ? (rz / *a.rz_old) : 0.0;
     for (int64_t i = (int64_t)lb * kBlock + threadIdx.x; i < a.n; i += (int64_t)grid * kBlock)
         a.p[i] = a.rz_old ? a.z[i] + beta * a.p[i] : a.z[i];
 }
@@ -709,14 +747,28 @@ struct CgUpdArgs {
     const double* p;
     const double* q;
     const double* rz;
-    const double* pq;
-    double* partial;  // r.r partial of block lb at partial[lb]
+    double* pq;
+    double* partial;     // r.r partial of block lb at partial[lb]
+    const double* part;  // if set: pq is the sum of part[0..npart), stored here
+    int npart;
 };
 
-__device__ __forceinline__ void cg_update_body(const CgUpdArgs& a, int lb, int grid, double* sh) {
+// x += alpha p, r -= alpha q, and the block's part of r.r; with `first` also
+// the next V-cycle's first smoother step from the new r (the operations of
+// smooth_first_body)
+template <typename T>
+__device__ __forceinline__ void cg_update_body(const CgUpdArgs& a, const SmoothFirstArgs<T>* first, int lb, int grid,
+                                               double* sh) {
     // a non-positive or non-finite curvature is a breakdown: leave x and r
     // unchanged so the caller keeps the last iterate
-    const double pqv = *a.pq, rzv = *a.rz;
+    double pqv;
+    if (a.part) {
+        pqv = finish_block(a.part, a.npart, sh);
+        if (lb == 0 && threadIdx.x == 0) *a.pq = pqv;
+    } else {
+        pqv = *a.pq;
+    }
+    const double rzv = *a.rz;
     const double alpha = (pqv > 0.0 && isfinite(pqv) && isfinite(rzv)) ? rzv / pqv : 0.0;
     double v = 0.0;
     for (int64_t i = (int64_t)lb * kBlock + threadIdx.x; i < a.n; i += (int64_t)grid * kBlock) {
@@ -724,16 +776,17 @@ __device__ __forceinline__ void cg_update_body(const CgUpdArgs& a, int lb, int g
         double ri = a.r[i] - alpha * a.q[i];
         a.r[i] = ri;
         v += ri * ri;
+        if (first) {
+            const T bi = (T)ri;
+            if (first->b64) first->b[i] = bi;
+            const T di = first->c2 * (first->dinv[i] * bi);
+            first->d[i] = di;
+            first->x[i] = di;
+        }
     }
     double t = block_sum(v, sh);
     if (threadIdx.x == 0) a.partial[lb] = t;
 }
-
-// *result = sum of partial[0..nb) (one block of kFinishThreads threads).
-// Thread t adds partial[t], partial[t + T], ... in ascending order, four
-// independent loads in flight at a time; the per-thread sums are combined
-// by a fixed tree.  The order depends on nb only.
-constexpr int kFinishThreads = 1024;
 
 struct FinishArgs {
     int nb;
