@@ -21,6 +21,8 @@ NO_CONTRACT = {"k_setup.hip", "k_spgemm.hip"}
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # leading scalar kernel arguments arrive in registers
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-result", "-Wno-unused-command-line-argument",
     "-I", os.path.join(HERE, "..", "include"),
 ]

@@ -181,7 +181,7 @@ constexpr int kRunWords = kMaxRuns + 2;
 
 // windows of columns kept per row-dictionary group (see DCsr::drun)
 constexpr int kDictRuns = 8;
-constexpr int kDictRunWords = 2 + 2 * kDictRuns;
+constexpr int kDictRunWords = 4 + 2 * kDictRuns;
 
 // CSR matrix resident on the device
 struct DCsr {
@@ -219,13 +219,14 @@ struct DCsr {
     DBuf<uint32_t> urun;
     // row dictionaries (k_rows.hip), or empty: groups of dk consecutive row
     // blocks store each distinct row (values and column offsets from the row)
-    // once.  Row r's is drow_of[r] of its group g's rows drow[g] .. drow[g+1],
-    // each start | length << 16 into the group's entries dent[g] .. dent[g+1].
-    // drun[kDictRunWords g ..]: the windows of columns the group gathers from
-    // (number, total length, then first column less the group's first row,
-    // and length, of each, ascending); number 0 where they are not staged.
+    // once.  Row r's is drow_of[r] of its group g's records in dinfo, each
+    // start | length << 16 into the group's entries in doff and dval.
+    // drun[kDictRunWords g ..]: where the group's rows and entries start
+    // (the next record holds their ends), then the windows of columns it
+    // gathers from: number, total length, and first column less
+    // the group's first row, and length, of each, ascending (number 0: none).
     DBuf<uint16_t> drow_of;
-    DBuf<int> drow, dent, doff, drun;
+    DBuf<int> doff, drun;
     DBuf<uint32_t> dinfo;
     DBuf<double> dval;
     DBuf<float> dval32;
@@ -243,7 +244,7 @@ struct DCsr {
     // bytes: the dictionaries and a 16-bit number per row, or values, columns
     // as stored, row pointer and block tables
     double stream_bytes(double size) const {
-        if (dk > 0) return 2.0 * n + (size + 4.0) * (double)de + 4.0 * (double)dn + (8.0 + 4.0 * kDictRunWords) * (dgroups() + 1);
+        if (dk > 0) return 2.0 * n + (size + 4.0) * (double)de + 4.0 * (double)dn + 4.0 * kDictRunWords * (dgroups() + 1);
         return (double)nnz * (size + col_bytes()) + 4.0 * (n + 1) + (col16 ? 4.0 * nblk : 0.0) + unique_bytes();
     }
     // column bytes per stored entry the streaming kernels read

@@ -160,14 +160,20 @@ __global__ __launch_bounds__(kBlock) void k_rows_fill(int nblk, int dk, const in
                                                       const int* first, const uint32_t* record, uint32_t* dinfo,
                                                       int* doff, double* dval, int* drun, int* result) {
     __shared__ int table[2 * kOffsets], list[kOffsets], sorted[kOffsets], count;
-    __shared__ int run[kDictRunWords];
+    __shared__ int run[kDictRunWords - 2];
     constexpr int kFree = 0x7fffffff;
     const int g = blockIdx.x;
     const int r0 = blk[g * dk], n = blk[min((g + 1) * dk, nblk)] - r0;
     const int m0 = drow[g], m = drow[g + 1] - m0, e0 = dent[g];
+    int* rec = drun + (size_t)g * kDictRunWords;
+    if (threadIdx.x < 2) {
+        rec[threadIdx.x] = threadIdx.x == 0 ? m0 : e0;
+        // the ends of the last group
+        if (g + 1 == (int)gridDim.x) rec[kDictRunWords + threadIdx.x] = threadIdx.x == 0 ? m0 + m : dent[g + 1];
+    }
     for (int i = threadIdx.x; i < 2 * kOffsets; i += kBlock) table[i] = kFree;
     if (threadIdx.x == 0) count = 0;
-    if (threadIdx.x < kDictRunWords) run[threadIdx.x] = 0;
+    if (threadIdx.x < kDictRunWords - 2) run[threadIdx.x] = 0;
     __syncthreads();
     // distinct offsets (a full table ends the search: not staged)
     for (int i = threadIdx.x >> 3; i < m; i += kBlock / 8) {
@@ -225,7 +231,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_fill(int nblk, int dk, const in
         }
         __syncthreads();
     }
-    if (threadIdx.x < kDictRunWords) drun[(size_t)g * kDictRunWords + threadIdx.x] = run[threadIdx.x];
+    if (threadIdx.x < kDictRunWords - 2) rec[2 + threadIdx.x] = run[threadIdx.x];
     for (int i = threadIdx.x >> 3; i < m; i += kBlock / 8) {
         const int r = first[r0 + i];
         const uint32_t rec = record[r0 + i];
@@ -244,8 +250,6 @@ void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s) {
     A.dk = 0;
     A.dn = A.de = 0;
     A.drow_of.release();
-    A.drow.release();
-    A.dent.release();
     A.drun.release();
     A.dinfo.release();
     A.doff.release();
@@ -264,33 +268,30 @@ void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s) {
         tmp(scan_tmp_size(groups), mc), result(R_WORDS + 2, mc);
     DBuf<uint32_t> record((size_t)A.n, mc);
     A.drow_of.alloc((size_t)A.n, mc);
-    A.drow.alloc((size_t)groups + 1, mc);
-    A.dent.alloc((size_t)groups + 1, mc);
+    DBuf<int> drow((size_t)groups + 1, mc), dent((size_t)groups + 1, mc);
     zero_async(result.get(), R_WORDS * sizeof(int), s);
     hipLaunchKernelGGL(k_rows_count, dim3(groups), dim3(kBlock), 0, s, A.nblk, dk, (const int*)A.blk.get(),
                        (const int*)A.rowptr.get(), (const int*)A.col.get(), (const double*)A.val.get(), A.drow_of.get(),
                        cnt_n.get(), cnt_e.get(), first.get(), record.get(), result.get());
     MATAMG_LAUNCH_CHECK();
-    exclusive_scan(cnt_n.get(), A.drow.get(), groups, tmp.get(), s);
-    exclusive_scan(cnt_e.get(), A.dent.get(), groups, tmp.get(), s);
-    MATAMG_HIP(hipMemcpyAsync(result.get() + R_WORDS, A.drow.get() + groups, sizeof(int), hipMemcpyDeviceToDevice, s));
-    MATAMG_HIP(hipMemcpyAsync(result.get() + R_WORDS + 1, A.dent.get() + groups, sizeof(int), hipMemcpyDeviceToDevice, s));
+    exclusive_scan(cnt_n.get(), drow.get(), groups, tmp.get(), s);
+    exclusive_scan(cnt_e.get(), dent.get(), groups, tmp.get(), s);
+    MATAMG_HIP(hipMemcpyAsync(result.get() + R_WORDS, drow.get() + groups, sizeof(int), hipMemcpyDeviceToDevice, s));
+    MATAMG_HIP(hipMemcpyAsync(result.get() + R_WORDS + 1, dent.get() + groups, sizeof(int), hipMemcpyDeviceToDevice, s));
     int res[R_WORDS + 2];
     d2h(res, result.get(), R_WORDS + 2, s);
     const int64_t dn = res[R_WORDS], de = res[R_WORDS + 1];
     if (res[R_FAIL] || de * kDictShare > A.nnz) {
         A.drow_of.release();
-        A.drow.release();
-        A.dent.release();
         return;
     }
     A.dinfo.alloc((size_t)dn, mc);
     A.doff.alloc((size_t)de, mc);
     A.dval.alloc((size_t)de, mc);
-    A.drun.alloc((size_t)groups * kDictRunWords, mc);
+    A.drun.alloc((size_t)(groups + 1) * kDictRunWords, mc);
     hipLaunchKernelGGL(k_rows_fill, dim3(groups), dim3(kBlock), 0, s, A.nblk, dk, (const int*)A.blk.get(),
                        (const int*)A.rowptr.get(), (const int*)A.col.get(), (const double*)A.val.get(),
-                       (const int*)A.drow.get(), (const int*)A.dent.get(), (const int*)first.get(),
+                       (const int*)drow.get(), (const int*)dent.get(), (const int*)first.get(),
                        (const uint32_t*)record.get(), A.dinfo.get(), A.doff.get(), A.dval.get(), A.drun.get(),
                        result.get());
     MATAMG_LAUNCH_CHECK();

@@ -242,36 +242,49 @@ std::vector<int> stream_blocks(const int* rp, int n, int group, int cap) {
 }
 
 namespace {
+// The tables that a block's first loads read come first, one by one: the
+// leading scalar arguments are in registers when a wavefront starts, while the
+// rest of the arguments is itself a load, which then runs beside the tables'
+// (the kernels of small levels are a chain of four or five memory latencies,
+// 3.5 to 5 us in all: a V-cycle of the 512^2 two-domain problem, 39 launches,
+// 187 -> 179 us).  No more than these: each argument also costs the host.
 template <typename T, int MODE, bool HAS_DOT, int G, int CAP = kStreamCap>
-__global__ __launch_bounds__(kBlock) void k_stream(SArgs<T> a, int nblk) {
+__global__ __launch_bounds__(kBlock) void k_stream(const int* blk, const int* blkk, int nblk, SArgs<T> a) {
     __shared__ StreamShared<T, CAP> S;
     const int bid = xcd_block(nblk);
     if (bid >= nblk) return;
+    a.blk = blk;
+    a.blkk = blkk;
     stream_block<T, MODE, HAS_DOT, G, CAP>(a, bid, S);
 }
 
 template <typename T, int MODE, bool HAS_DOT>
-__global__ __launch_bounds__(kBlock) void k_rows(SArgs<T> a, int groups, RowsSize z) {
+__global__ __launch_bounds__(kBlock) void k_rows(const int* blk, const int* drun, int groups, SArgs<T> a, RowsSize z) {
     extern __shared__ char lds[];
     const int g = xcd_block(groups);
     if (g >= groups) return;
+    a.blk = blk;
+    a.drun = drun;
     rows_group<T, MODE, HAS_DOT>(a, g, z, lds);
 }
 
 template <typename T, int MODE, bool HAS_DOT>
 void launch_stream(const DCsr& A, const SArgs<T>& a, hipStream_t s) {
     if (A.nblk <= 0) return;
+    auto stream = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s, a.blk, a.blkk, A.nblk, a);
+    };
     if (a.dk > 0) {
         const RowsSize z = rows_size<T>(A.dmax_e, A.dmax_n, A.dmax_x, HAS_DOT ? a.dk * kMaxRowsPerBlock : 0);
         hipLaunchKernelGGL((k_rows<T, MODE, HAS_DOT>), dim3(xcd_grid(A.dgroups())), dim3(kBlock), rows_lds<T>(z).bytes,
-                           s, a, A.dgroups(), z);
-    } else if (A.group == 1 && A.cap == kStreamCapWide)
-        hipLaunchKernelGGL((k_stream<T, MODE, HAS_DOT, 1, kStreamCapWide>), dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s,
-                           a, A.nblk);
-    else if (A.group == 1)
-        hipLaunchKernelGGL((k_stream<T, MODE, HAS_DOT, 1>), dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s, a, A.nblk);
-    else
-        hipLaunchKernelGGL((k_stream<T, MODE, HAS_DOT, 8>), dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s, a, A.nblk);
+                           s, a.blk, a.drun, A.dgroups(), a, z);
+    } else if (A.group == 1 && A.cap == kStreamCapWide) {
+        stream(k_stream<T, MODE, HAS_DOT, 1, kStreamCapWide>);
+    } else if (A.group == 1) {
+        stream(k_stream<T, MODE, HAS_DOT, 1>);
+    } else {
+        stream(k_stream<T, MODE, HAS_DOT, 8>);
+    }
     MATAMG_LAUNCH_CHECK();
     if (HAS_DOT && a.dt.result) finish_sum(a.dt, stream_partials(A), s);
 }

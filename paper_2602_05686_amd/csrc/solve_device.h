@@ -54,8 +54,6 @@ struct SArgs {
     // row dictionaries (dk > 0: val, col, ... above are not read)
     int dk, nblk;
     const uint16_t* drow_of;
-    const int* drow;
-    const int* dent;
     const uint32_t* dinfo;
     const int* doff;
     const int* drun;
@@ -544,8 +542,9 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
     double* ld = reinterpret_cast<double*>(lds);
     const int b0 = g * a.dk, b1 = min(b0 + a.dk, a.nblk);
     const int r0 = a.blk[b0], r1 = a.blk[b1];
-    const int m0 = a.drow[g], m1 = a.drow[g + 1], e0 = a.dent[g], e1 = a.dent[g + 1];
-    const int* run = a.drun + (size_t)g * kDictRunWords;
+    const int* rec = a.drun + (size_t)g * kDictRunWords;
+    const int m0 = rec[0], m1 = rec[kDictRunWords], e0 = rec[1], e1 = rec[kDictRunWords + 1];
+    const int* run = rec + 2;
     const int nrun = z.max_x > 0 ? run[0] : 0, total = run[1];
     const int first = r0 + (int)threadIdx.x;
     // the first row's record number and operands travel with the dictionary
@@ -648,8 +647,6 @@ inline void dict_args(const DCsr& M, const T* dval, SArgs<T>& a) {
     a.nblk = M.nblk;
     a.n = M.m;
     a.drow_of = M.drow_of.get();
-    a.drow = M.drow.get();
-    a.dent = M.dent.get();
     a.dinfo = M.dinfo.get();
     a.doff = M.doff.get();
     a.drun = M.drun.get();
