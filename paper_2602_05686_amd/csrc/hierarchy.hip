@@ -106,20 +106,29 @@ int read_flag(int* dflag, hipStream_t s) {
     return v;
 }
 
-// lambda = ||dscale .* (A v)|| after `iters` normalised steps from a seeded start
-double power_method(const DCsr& A, const double* dscale, int iters, uint64_t key, Hierarchy& h, hipStream_t s) {
-    const int n = A.n;
+// *nrm2 (device) = ||dscale .* (A v)||^2 after `iters` normalised steps from a
+// seeded start (iters > 0).  One launch a step: the norm of the step before is
+// taken from its partial sums by the product that needs it (from the finished
+// sum of very many), which scales the vector as it gathers.
+void power_method(const DCsr& A, const double* dscale, int iters, uint64_t key, double* nrm2, Hierarchy& h,
+                  hipStream_t s) {
+    const int n = A.n, nb = stream_partials(A), n0 = vector_partials(n);
     DBuf<double> v((size_t)n, &h.mem), w((size_t)n, &h.mem);
-    fill_seeded_uniform(n, key, v.get(), s);
-    dot<double>(v.get(), v.get(), n, h.partial.get(), h.counter.get(), h.scal.get() + S_TMP, s);
-    scale_by_inv_norm(n, h.scal.get() + S_TMP, v.get(), v.get(), s);
+    DBuf<double> p((size_t)std::max(nb, n0), &h.mem), q((size_t)std::max(nb, n0), &h.mem);
+    // the sums stay partial where the next product can take them itself
+    auto target = [&](double* part, int count, bool last) {
+        return DotTarget{part, nullptr, last || count > kOwnSumPartials ? nrm2 : nullptr};
+    };
+    double *x = v.get(), *y = w.get(), *px = p.get(), *py = q.get();
+    fill_seeded_uniform(n, key, x, target(px, n0, false), s);
+    int np = n0;
     for (int it = 0; it < iters; ++it) {
-        spmv_scale_norm(A, v.get(), dscale, w.get(), h.dt(S_TMP), s);
-        if (it + 1 < iters) scale_by_inv_norm(n, h.scal.get() + S_TMP, w.get(), v.get(), s);
+        const bool whole = np > kOwnSumPartials;
+        spmv_scale_norm(A, x, whole ? nrm2 : px, whole ? 1 : np, dscale, y, target(py, nb, it + 1 == iters), s);
+        np = nb;
+        std::swap(x, y);
+        std::swap(px, py);
     }
-    double nrm2 = 0.0;
-    d2h(&nrm2, h.scal.get() + S_TMP, 1, s);
-    return iters > 0 ? std::sqrt(nrm2) : 0.0;
 }
 
 void smoother_coefficients(Level& L, const amg_options& o) {
@@ -314,8 +323,12 @@ void smoothed_prolongator(Hierarchy& h, int l, const DCsr& F, const double* dt, 
     MemCounter* mc = &h.mem;
     const int nl = L.A.n;
     DBuf<int> cnt(nl, mc), tmp(scan_tmp_size(nl), mc);
-    ensure_partial(h, std::max(stream_partials(F), stream_partials(L.A)));
-    L.lam_pf = power_method(F, dtinv, opt.power_iters, stream_key(opt.seed, kPurposePf, l), h, s);
+    double nrm2 = 0.0;
+    if (opt.power_iters > 0) {
+        power_method(F, dtinv, opt.power_iters, stream_key(opt.seed, kPurposePf, l), h.scal.get() + S_TMP, h, s);
+        d2h(&nrm2, h.scal.get() + S_TMP, 1, s);
+    }
+    L.lam_pf = std::sqrt(nrm2);
     L.omega = L.lam_pf > 0.0 ? opt.omega_sym / L.lam_pf : 0.0;
     DCsr Ph;
     Ph.n = nl;
@@ -335,11 +348,19 @@ void smoothed_prolongator(Hierarchy& h, int l, const DCsr& F, const double* dt, 
 
 // Chebyshev bounds and coefficients of every smoothing level
 void smoother_bounds(Hierarchy& h, hipStream_t s) {
-    for (int k = 0; k + 1 < h.nlev; ++k) {
-        Level& L = h.lev[k];
-        L.lam_cheb = power_method(L.A, L.dinv.get(), h.opt.power_iters, stream_key(h.opt.seed, kPurposeCheb, k), h,
-                                  s);
-        smoother_coefficients(L, h.opt);
+    // one read-back for all levels
+    const int count = h.nlev - 1, iters = h.opt.power_iters;
+    std::vector<double> nrm2((size_t)count, 0.0);
+    if (count > 0 && iters > 0) {
+        DBuf<double> dev((size_t)count, &h.mem);
+        for (int k = 0; k < count; ++k)
+            power_method(h.lev[k].A, h.lev[k].dinv.get(), iters, stream_key(h.opt.seed, kPurposeCheb, k),
+                         dev.get() + k, h, s);
+        d2h(nrm2.data(), dev.get(), (size_t)count, s);
+    }
+    for (int k = 0; k < count; ++k) {
+        h.lev[k].lam_cheb = std::sqrt(nrm2[k]);
+        smoother_coefficients(h.lev[k], h.opt);
     }
 }
 
@@ -584,7 +605,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
         // distance-2 maximal independent set, synchronous rounds
         {
             DBuf<uint8_t> state(nl, mc);
-            DBuf<uint64_t> t1(nl, mc), t2(nl, mc);
+            DBuf<uint64_t> t1(nl, mc);
             // rounds run in batches with one read-back per batch: a round
             // after the last undecided node is gone changes nothing, and the
             // per-round undecided counts give the exact round count
@@ -596,7 +617,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
             for (bool done = false; !done;) {
                 zero_async(und.get(), sizeof(int) * kMisBatch, s);
                 for (int j = 0; j < kMisBatch; ++j)
-                    mis_round(F, nullptr, key, state.get(), t1.get(), t2.get(), und.get() + j, s);
+                    mis_round(F, nullptr, key, state.get(), t1.get(), und.get() + j, s);
                 int left[kMisBatch];
                 d2h(left, und.get(), kMisBatch, s);
                 for (int j = 0; j < kMisBatch && !done; ++j) {
@@ -607,7 +628,6 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
             }
             L.mis_rounds = rounds;
             t1.release();
-            t2.release();
             DBuf<int> flags(nl, mc), rank((size_t)nl + 1, mc), tmp(scan_tmp_size(nl), mc), phase2(nl, mc);
             agg_root_flags(nl, state.get(), flags.get(), s);
             exclusive_scan(flags.get(), rank.get(), nl, tmp.get(), s);

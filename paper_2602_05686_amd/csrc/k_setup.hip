@@ -463,18 +463,37 @@ __global__ void k_mis_init(int n, const uint8_t* dir, uint8_t* state) {
     ROW_LOOP(i, n) state[i] = (dir && dir[i]) ? MIS_OUT : MIS_UND;
 }
 
-// T_out(i) = max over i and its kept neighbours of T_in, where T_in is the
-// packed tuple of the node state (FIRST) or the previous hop's result
+// T(i) = max over i and its kept neighbours of T_in.  FIRST: T_in is the
+// packed tuple of the node state and T goes to tout; otherwise T_in is the
+// first hop's result, T decides node i, and the nodes left undecided are
+// counted (a second hop gathers only T_in, so the states may change under it:
+// a pass of its own for the decision cost 3 to 9 us a round).
 template <bool FIRST>
 __global__ __launch_bounds__(kBlock) void k_mis_hop(const int* rowptr, const int* col, const uint8_t* mask,
-                                                    const int* blk, int nblk, uint64_t key, const uint8_t* state,
-                                                    const uint64_t* tin, uint64_t* tout) {
+                                                    const int* blk, int nblk, uint64_t key, uint8_t* state,
+                                                    const uint64_t* tin, uint64_t* tout, int* undecided) {
     __shared__ uint64_t tv[kStreamCap];
     __shared__ uint64_t tred[kBlock / 64];
     const int bid = xcd_block(nblk);
     if (bid >= nblk) return;
     const RowBlock rb = row_block(rowptr, blk, bid);
     auto tuple_at = [&](int j) -> uint64_t { return FIRST ? tuple_of(state[j], key, j) : tin[j]; };
+    // node i's maximum is t: stored, or the node's state decided by it;
+    // whether the node stays undecided
+    auto result = [&](int i, uint64_t t) -> bool {
+        if constexpr (FIRST) {
+            tout[i] = t;
+            return false;
+        } else {
+            uint8_t st = state[i];
+            if (st != MIS_UND) return false;
+            if (t == tuple_of(st, key, i)) st = MIS_IN;
+            else if ((t >> 62) == MIS_IN) st = MIS_OUT;
+            state[i] = st;
+            return st == MIS_UND;
+        }
+    };
+    bool und = false;
     if (!rb.longrow) {
         // all column and mask loads first (indices past the block's end
         // clamped to its last entry), then all neighbour gathers, then the
@@ -508,7 +527,7 @@ __global__ __launch_bounds__(kBlock) void k_mis_hop(const int* rowptr, const int
                 const uint64_t v = tv[k - rb.k0];
                 best = v > best ? v : best;
             }
-            tout[r] = best;
+            und = result(r, best);
         }
     } else {
         uint64_t best = 0ull;
@@ -528,29 +547,13 @@ __global__ __launch_bounds__(kBlock) void k_mis_hop(const int* rowptr, const int
         if (threadIdx.x == 0) {
             uint64_t b = tuple_at(rb.r0);
             for (int w = 0; w < kBlock / 64; ++w) b = tred[w] > b ? tred[w] : b;
-            tout[rb.r0] = b;
+            und = result(rb.r0, b);
         }
     }
-}
-
-__global__ void k_mis_update(int n, uint64_t key, const uint64_t* t2, uint8_t* state, int* undecided) {
-    __shared__ int cnt;
-    if (threadIdx.x == 0) cnt = 0;
-    __syncthreads();
-    int local = 0;
-    ROW_LOOP(i, n) {
-        uint8_t st = state[i];
-        if (st != MIS_UND) continue;
-        const uint64_t own = tuple_of(st, key, (int)i);
-        const uint64_t t = t2[i];
-        if (t == own) st = MIS_IN;
-        else if ((t >> 62) == MIS_IN) st = MIS_OUT;
-        state[i] = st;
-        local += (st == MIS_UND);
+    if constexpr (!FIRST) {
+        const int left = __syncthreads_count(und);
+        if (threadIdx.x == 0 && left) atomicAdd(undecided, left);
     }
-    if (local) atomicAdd(&cnt, local);
-    __syncthreads();
-    if (threadIdx.x == 0 && cnt) atomicAdd(undecided, cnt);
 }
 
 __global__ void k_root_flags(int n, const uint8_t* state, int* flags) {
@@ -1065,19 +1068,15 @@ void cut_drop(const DCsr& A, const uint8_t* dir, const double* lval, const doubl
 
 void mis_init(int n, const uint8_t* dir, uint8_t* state, hipStream_t s) { LAUNCH(k_mis_init, n, n, dir, state); }
 
-void mis_round(const DCsr& A, const uint8_t* mask, uint64_t key, uint8_t* state, uint64_t* t1, uint64_t* t2,
-               int* undecided, hipStream_t s) {
-    const int n = A.n;
-    if (A.setup_nblk() > 0) {
-        hipLaunchKernelGGL((k_mis_hop<true>), dim3(xcd_grid(A.setup_nblk())), dim3(kBlock), 0, s, A.rowptr.get(),
-                           A.col.get(), mask, A.setup_blk(), A.setup_nblk(), key, (const uint8_t*)state, (const uint64_t*)nullptr,
-                           t1);
-        hipLaunchKernelGGL((k_mis_hop<false>), dim3(xcd_grid(A.setup_nblk())), dim3(kBlock), 0, s, A.rowptr.get(),
-                           A.col.get(), mask, A.setup_blk(), A.setup_nblk(), key, (const uint8_t*)state, (const uint64_t*)t1,
-                           t2);
-        MATAMG_LAUNCH_CHECK();
-    }
-    LAUNCH(k_mis_update, n, n, key, t2, state, undecided);
+void mis_round(const DCsr& A, const uint8_t* mask, uint64_t key, uint8_t* state, uint64_t* t1, int* undecided,
+               hipStream_t s) {
+    if (A.setup_nblk() <= 0) return;
+    const dim3 grid(xcd_grid(A.setup_nblk()));
+    hipLaunchKernelGGL((k_mis_hop<true>), grid, dim3(kBlock), 0, s, A.rowptr.get(), A.col.get(), mask, A.setup_blk(),
+                       A.setup_nblk(), key, state, (const uint64_t*)nullptr, t1, (int*)nullptr);
+    hipLaunchKernelGGL((k_mis_hop<false>), grid, dim3(kBlock), 0, s, A.rowptr.get(), A.col.get(), mask, A.setup_blk(),
+                       A.setup_nblk(), key, state, (const uint64_t*)t1, (uint64_t*)nullptr, undecided);
+    MATAMG_LAUNCH_CHECK();
 }
 
 void agg_root_flags(int n, const uint8_t* state, int* flags, hipStream_t s) {

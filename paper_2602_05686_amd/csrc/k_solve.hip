@@ -376,9 +376,11 @@ void spmv_resid_norm(const DCsr& A, const double* x, const double* b, double* y,
     launch_stream<double, M_RESNORM, true>(A, a, s);
 }
 
-void spmv_scale_norm(const DCsr& A, const double* x, const double* dscale, double* y, DotTarget dt,
-                     hipStream_t s) {
+void spmv_scale_norm(const DCsr& A, const double* x, const double* part, int npart, const double* dscale, double* y,
+                     DotTarget dt, hipStream_t s) {
     auto a = base_args<double>(A, A.val.get(), x);
+    a.b = part;
+    a.npart = npart;
     a.dinv = dscale;
     a.y = y;
     a.dt = dt;
@@ -402,13 +404,6 @@ namespace {
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_smooth_first(SmoothFirstArgs<T> a) {
     smooth_first_body(a, blockIdx.x, gridDim.x);
-}
-
-__global__ __launch_bounds__(kBlock) void k_scale_inv_norm(int64_t n, const double* nrm2, const double* in,
-                                                           double* out) {
-    const double inv = 1.0 / sqrt(*nrm2);
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
-        out[i] = in[i] * inv;
 }
 
 template <typename T, bool FIRST>
@@ -449,12 +444,18 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
     return z ^ (z >> 31);
 }
 
-__global__ __launch_bounds__(kBlock) void k_seeded_uniform(int64_t n, uint64_t key, double* v) {
+// seeded values in (-1, 1), and their squares summed as k_dot sums a vector's
+__global__ __launch_bounds__(kBlock) void k_seeded_uniform(int64_t n, uint64_t key, double* v, DotTarget dt) {
+    __shared__ double sh[kBlock / 64];
+    double t = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
         uint64_t h = splitmix64(key ^ (uint64_t)i);
         double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
-        v[i] = 2.0 * u - 1.0;
+        const double x = 2.0 * u - 1.0;
+        v[i] = x;
+        t += x * x;
     }
+    store_partial(block_sum(t, sh), dt);
 }
 }  // namespace
 
@@ -469,12 +470,6 @@ template void smooth_first<double>(int64_t, const double*, double*, const double
                                    hipStream_t);
 template void smooth_first<float>(int64_t, const double*, float*, const float*, float, float*, float*,
                                   hipStream_t);
-
-void scale_by_inv_norm(int64_t n, const double* nrm2, const double* in, double* out, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_scale_inv_norm, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, nrm2, in, out);
-    MATAMG_LAUNCH_CHECK();
-}
 
 template <typename T>
 void cg_update(int64_t n, double* x, double* r, const double* p, const double* q, const double* rz, double* pq,
@@ -521,10 +516,13 @@ void cast_vec(int64_t n, const A* in, B* out, hipStream_t s) {
 template void cast_vec<double, float>(int64_t, const double*, float*, hipStream_t);
 template void cast_vec<float, double>(int64_t, const float*, double*, hipStream_t);
 
-void fill_seeded_uniform(int64_t n, uint64_t key, double* v, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_seeded_uniform, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, key, v);
+int fill_seeded_uniform(int64_t n, uint64_t key, double* v, DotTarget dt, hipStream_t s) {
+    if (n <= 0) return 0;
+    const int g = vec_grid(n);
+    hipLaunchKernelGGL(k_seeded_uniform, dim3(g), dim3(kBlock), 0, s, n, key, v, dt);
     MATAMG_LAUNCH_CHECK();
+    if (dt.result) finish_sum(dt, g, s);
+    return g;
 }
 
 // =================================================================== dense

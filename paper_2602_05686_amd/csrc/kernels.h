@@ -76,17 +76,16 @@ void spmv_restrict_first(const DCsr& R, const T* val, const T* r, T* bc, const T
 void spmv_dot(const DCsr& A, const double* p, double* q, DotTarget dt, hipStream_t s);
 // y = b - A x and sum_i y_i^2
 void spmv_resid_norm(const DCsr& A, const double* x, const double* b, double* y, DotTarget dt, hipStream_t s);
-// y = dscale .* (A x) and sum y_i^2 (power method)
-void spmv_scale_norm(const DCsr& A, const double* x, const double* dscale, double* y, DotTarget dt,
-                     hipStream_t s);
+// y = dscale .* (A x / |x|) and sum y_i^2 (power method); x.x is the sum of
+// part[0..npart), at most kOwnSumPartials of them
+void spmv_scale_norm(const DCsr& A, const double* x, const double* part, int npart, const double* dscale, double* y,
+                     DotTarget dt, hipStream_t s);
 
 // --------------------------------------------------------------- vectors ---
 // first smoother step from zero: d = c2 * dinv .* b; x = d.  If b64 is given,
 // b = (T) b64 is also stored to `b`.
 template <typename T>
 void smooth_first(int64_t n, const double* b64, T* b, const T* dinv, T c2, T* d, T* x, hipStream_t s);
-// v = v / sqrt(*nrm2)
-void scale_by_inv_norm(int64_t n, const double* nrm2, const double* in, double* out, hipStream_t s);
 // most partials that a kernel which needs their sum adds up itself
 constexpr int kOwnSumPartials = 1024;
 // the finest level's first smoother step from zero, as smooth_first takes it
@@ -117,7 +116,9 @@ void finish_report(const DotTarget& dt, int nblocks, const double* scal, int wor
                    unsigned* host_step, hipStream_t s);
 template <typename A, typename B>
 void cast_vec(int64_t n, const A* in, B* out, hipStream_t s);
-void fill_seeded_uniform(int64_t n, uint64_t key, double* v, hipStream_t s);
+// seeded values in (-1, 1) and sum_i v_i^2 as dot(v, v) takes it; its number
+// of partial sums is returned (all that is left if dt.result is null)
+int fill_seeded_uniform(int64_t n, uint64_t key, double* v, DotTarget dt, hipStream_t s);
 
 // ----------------------------------------------------------------- dense ---
 // out = Minv * in for a dense row-major n x n FP64 matrix; in/out of type T

@@ -40,8 +40,8 @@ void mis_init(int n, const uint8_t* dir, uint8_t* state, hipStream_t s);
 // one synchronous round over the entries mask keeps (nullptr: every stored
 // entry); *undecided (device, zero on entry) receives the number of nodes
 // still undecided
-void mis_round(const DCsr& A, const uint8_t* mask, uint64_t key, uint8_t* state, uint64_t* t1, uint64_t* t2,
-               int* undecided, hipStream_t s);
+void mis_round(const DCsr& A, const uint8_t* mask, uint64_t key, uint8_t* state, uint64_t* t1, int* undecided,
+               hipStream_t s);
 void agg_root_flags(int n, const uint8_t* state, int* flags, hipStream_t s);
 // phase 2 (neighbours of roots) and phase 3 (leftovers) over the entries
 // mask keeps (nullptr: every stored entry); list: n ints and nlist: one int

@@ -41,7 +41,7 @@ struct SArgs {
     const uint16_t* uoff;    // block b's are uoff[ustart[b] .. ustart[b+1])
     const uint32_t* urun;    // or their runs (DCsr::urun; null: none)
     const T* x;        // gathered operand
-    const T* b;        // right-hand side (RESID, SMOOTH, RESNORM)
+    const T* b;        // right-hand side (RESID, SMOOTH, RESNORM); SCALENORM: partial sums of x.x
     const T* yin;      // ADD: base vector; SMOOTH: iterate at the row
     const T* dinv;     // SMOOTH: inverse diagonal; SCALENORM: row scale
     T* d;              // SMOOTH: direction (in/out); RESTRICT: direction (out)
@@ -58,7 +58,8 @@ struct SArgs {
     const int* doff;
     const int* drun;
     const T* dval;
-    int n;  // length of the gathered operand
+    int n;      // length of the gathered operand
+    int npart;  // SCALENORM: number of partial sums in b
 };
 
 // Per-row operands of the epilogue, loaded before the row's sum is known so
@@ -123,6 +124,53 @@ __device__ __forceinline__ double epilogue(const SArgs<T>& a, int r, T s, const 
     return dp;
 }
 
+// The sum of partial[0..nb) is taken by kFinishThreads threads: thread t adds
+// partial[t], partial[t + kFinishThreads], ... in ascending order, and the
+// per-thread sums are combined by a fixed tree.  The order depends on nb only.
+constexpr int kFinishThreads = 1024;
+constexpr int kFinishWaves = kFinishThreads / 64;
+
+// The same sum of at most kFinishThreads partials, by a block of kBlock
+// threads, on every thread: a kernel that needs a sum of few partials takes
+// it itself, in each of its blocks, instead of waiting for a launch of its
+// own (3 to 4 us, of about 100 us a CG step on small systems).  sh:
+// kFinishWaves doubles.
+__device__ __forceinline__ double finish_block(const double* partial, int nb, double* sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < kFinishThreads / kBlock; ++j) {
+        const int t = (int)threadIdx.x + j * kBlock;
+        double v = 0.0;
+        if (t < nb) v += partial[t];
+        v = wave_sum(v);
+        if (lane == 0) sh[w + j * (kBlock / 64)] = v;
+    }
+    __syncthreads();
+    double t = sh[0];
+    for (int k = 1; k < kFinishWaves; ++k) t += sh[k];
+    __syncthreads();
+    return t;
+}
+
+// The factor on the gathered operand: 1 / |x| in the power method, whose
+// iterates are scaled where the next product reads them (a pass of its own
+// over the vector and one for the sum cost the setup two launches in three).
+// x.x comes as its partial sums, or as one finished sum of very many.
+template <typename T, int MODE>
+__device__ __forceinline__ T operand_scale(const SArgs<T>& a, void* sh) {
+    if constexpr (MODE == M_SCALENORM) {
+        const double nrm2 = a.npart == 1 ? *a.b : finish_block(a.b, a.npart, reinterpret_cast<double*>(sh));
+        return 1.0 / sqrt(nrm2);
+    } else {
+        return T(1);
+    }
+}
+template <int MODE, typename T>
+__device__ __forceinline__ T operand(T x, T scale) {
+    if constexpr (MODE == M_SCALENORM) return x * scale;
+    else return x;
+}
+
 constexpr int kPerThread = kStreamCap / kBlock;
 
 // LDS of one streaming block of at most CAP stored entries: the products
@@ -156,8 +204,8 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ int stage_head(int k0, int cnt) { return cnt > 0 ? (k0 & 1) : 0; }
 
-template <typename T, int NP, int UQ>
-__device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, int cnt, T* prod) {
+template <typename T, int MODE, int NP, int UQ>
+__device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, int cnt, T scale, T* prod) {
     using P2 = typename PairOf<T>::type;
     const int base = a.cbase[bid];
     const int head = stage_head(k0, cnt);  // entry 0 alone when the block starts at an odd position
@@ -230,7 +278,7 @@ __device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, 
 #pragma unroll
         for (int q = 0; q < UQ; ++q) {
             const int j = tid + q * kBlock;
-            if (j < nu) xs[j] = xv[q];
+            if (j < nu) xs[j] = operand<MODE>(xv[q], scale);
         }
         __syncthreads();
 #pragma unroll
@@ -243,10 +291,10 @@ __device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, 
     } else {
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
-            x0[u] = a.x[base + (int)c[u].x];
-            x1[u] = a.x[base + (int)c[u].y];
+            x0[u] = operand<MODE>(a.x[base + (int)c[u].x], scale);
+            x1[u] = operand<MODE>(a.x[base + (int)c[u].y], scale);
         }
-        if (ts >= 0) xsng = a.x[base + cs];
+        if (ts >= 0) xsng = operand<MODE>(a.x[base + cs], scale);
     }
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
@@ -259,22 +307,20 @@ __device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, 
     if (ts >= 0) prod[ts] = vs * xsng;
 }
 
-template <typename T, int NU, bool PACKED>
-__device__ __forceinline__ void stage_products(const SArgs<T>& a, int bid, int k0, int cnt, T* prod) {
+template <typename T, int MODE, int NU>
+__device__ __forceinline__ void stage_products(const SArgs<T>& a, int k0, int cnt, T scale, T* prod) {
     int c[NU];
     T v[NU];
-    const int base = PACKED ? a.cbase[bid] : 0;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
         const int t = (int)threadIdx.x + u * kBlock;
         const int tc = t < cnt ? t : cnt - 1;
-        if constexpr (PACKED) c[u] = base + (int)__builtin_nontemporal_load(a.col16 + k0 + tc);
-        else c[u] = __builtin_nontemporal_load(a.col + k0 + tc);
+        c[u] = __builtin_nontemporal_load(a.col + k0 + tc);
         v[u] = __builtin_nontemporal_load(a.val + k0 + tc);
     }
     T xv[NU];
 #pragma unroll
-    for (int u = 0; u < NU; ++u) xv[u] = a.x[c[u]];
+    for (int u = 0; u < NU; ++u) xv[u] = operand<MODE>(a.x[c[u]], scale);
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
         const int t = (int)threadIdx.x + u * kBlock;
@@ -315,6 +361,7 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
     const int r0 = a.blk[bid], r1 = a.blk[bid + 1];
     const int k0 = a.blkk[bid], k1 = a.blkk[bid + 1];
     const int cnt = k1 - k0;
+    const T scale = operand_scale<T, MODE>(a, S.prod);
     double dp = 0.0;
     if (!(r1 - r0 == 1 && cnt > long_row_limit(G))) {
         const int gl = (int)threadIdx.x % G;
@@ -349,18 +396,18 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         if (a.col16) {
             // pairs of entries: ceil(pairs / kBlock) strides (block-uniform)
             switch (((cnt - stage_head(k0, cnt)) / 2 + kBlock - 1) / kBlock) {
-                case 0: stage_pairs<T, 0, kUQ>(a, bid, k0, cnt, S.prod); break;
-                case 1: stage_pairs<T, 1, kUQ>(a, bid, k0, cnt, S.prod); break;
-                case 2: stage_pairs<T, 2, kUQ>(a, bid, k0, cnt, S.prod); break;
-                case 3: stage_pairs<T, 3, kUQ>(a, bid, k0, cnt, S.prod); break;
-                case 4: stage_pairs<T, 4, kUQ>(a, bid, k0, cnt, S.prod); break;
+                case 0: stage_pairs<T, MODE, 0, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                case 1: stage_pairs<T, MODE, 1, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                case 2: stage_pairs<T, MODE, 2, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                case 3: stage_pairs<T, MODE, 3, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                case 4: stage_pairs<T, MODE, 4, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
                 default:
                     if constexpr (CAP > kStreamCap) {
                         switch (((cnt - stage_head(k0, cnt)) / 2 + kBlock - 1) / kBlock) {
-                            case 5: stage_pairs<T, 5, kUQ>(a, bid, k0, cnt, S.prod); break;
-                            case 6: stage_pairs<T, 6, kUQ>(a, bid, k0, cnt, S.prod); break;
-                            case 7: stage_pairs<T, 7, kUQ>(a, bid, k0, cnt, S.prod); break;
-                            case 8: stage_pairs<T, 8, kUQ>(a, bid, k0, cnt, S.prod); break;
+                            case 5: stage_pairs<T, MODE, 5, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 6: stage_pairs<T, MODE, 6, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 7: stage_pairs<T, MODE, 7, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 8: stage_pairs<T, MODE, 8, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
                             default: break;
                         }
                     }
@@ -369,14 +416,14 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         } else if constexpr (CAP == kStreamCap) {
             // (wide blocks are only made for packed matrices)
             switch (nu) {
-                case 1: stage_products<T, 1, false>(a, bid, k0, cnt, S.prod); break;
-                case 2: stage_products<T, 2, false>(a, bid, k0, cnt, S.prod); break;
-                case 3: stage_products<T, 3, false>(a, bid, k0, cnt, S.prod); break;
-                case 4: stage_products<T, 4, false>(a, bid, k0, cnt, S.prod); break;
-                case 5: stage_products<T, 5, false>(a, bid, k0, cnt, S.prod); break;
-                case 6: stage_products<T, 6, false>(a, bid, k0, cnt, S.prod); break;
-                case 7: stage_products<T, 7, false>(a, bid, k0, cnt, S.prod); break;
-                case 8: stage_products<T, 8, false>(a, bid, k0, cnt, S.prod); break;
+                case 1: stage_products<T, MODE, 1>(a, k0, cnt, scale, S.prod); break;
+                case 2: stage_products<T, MODE, 2>(a, k0, cnt, scale, S.prod); break;
+                case 3: stage_products<T, MODE, 3>(a, k0, cnt, scale, S.prod); break;
+                case 4: stage_products<T, MODE, 4>(a, k0, cnt, scale, S.prod); break;
+                case 5: stage_products<T, MODE, 5>(a, k0, cnt, scale, S.prod); break;
+                case 6: stage_products<T, MODE, 6>(a, k0, cnt, scale, S.prod); break;
+                case 7: stage_products<T, MODE, 7>(a, k0, cnt, scale, S.prod); break;
+                case 8: stage_products<T, MODE, 8>(a, k0, cnt, scale, S.prod); break;
                 default: break;
             }
         }
@@ -441,13 +488,13 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
                 v[u] = a.val[k];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) xv[u] = a.x[c[u]];
+            for (int u = 0; u < 4; ++u) xv[u] = operand<MODE>(a.x[c[u]], scale);
 #pragma unroll
             for (int u = 0; u < 4; ++u) s += v[u] * xv[u];
         }
         for (; t < cnt; t += kBlock) {
             const int k = k0 + t;
-            s += a.val[k] * a.x[col ? col[k] : base + (int)a.col16[k]];
+            s += a.val[k] * operand<MODE>(a.x[col ? col[k] : base + (int)a.col16[k]], scale);
         }
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
         for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
@@ -546,6 +593,7 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
     const int m0 = rec[0], m1 = rec[kDictRunWords], e0 = rec[1], e1 = rec[kDictRunWords + 1];
     const int* run = rec + 2;
     const int nrun = z.max_x > 0 ? run[0] : 0, total = run[1];
+    const T scale = operand_scale<T, MODE>(a, lds);
     const int first = r0 + (int)threadIdx.x;
     // the first row's record number and operands travel with the dictionary
     int id = 0;
@@ -571,7 +619,7 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
             for (int j = 1; j < kDictRuns; ++j)
                 if (j < nrun && i >= end[j - 1]) c = shift[j];
             c += i;
-            xs[i] = a.x[min(max(c, 0), a.n - 1)];  // (columns outside the matrix are in no entry)
+            xs[i] = operand<MODE>(a.x[min(max(c, 0), a.n - 1)], scale);  // (columns outside the matrix are in no entry)
         }
         // an entry's operand for row r0 + i is at place lo + i
         for (int e = threadIdx.x; e < e1 - e0; e += kBlock) {
@@ -604,7 +652,7 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
             s = row_sum<T>(lv, k0, len, [&](int k) { return x[lo[k]]; });
         } else {
             const T* x = a.x + r;
-            s = row_sum<T>(lv, k0, len, [&](int k) { return x[lo[k]]; });
+            s = row_sum<T>(lv, k0, len, [&](int k) { return operand<MODE>(x[lo[k]], scale); });
         }
         const double dp = epilogue<T, MODE, HAS_DOT>(a, r, s, o);
         if constexpr (HAS_DOT) ld[r - r0] = dp;
@@ -683,35 +731,6 @@ __device__ __forceinline__ void smooth_first_body(const SmoothFirstArgs<T>& a, i
         a.d[i] = di;
         a.x[i] = di;
     }
-}
-
-// *result = sum of partial[0..nb) (one block of kFinishThreads threads).
-// Thread t adds partial[t], partial[t + T], ... in ascending order, four
-// independent loads in flight at a time; the per-thread sums are combined
-// by a fixed tree.  The order depends on nb only.
-constexpr int kFinishThreads = 1024;
-constexpr int kFinishWaves = kFinishThreads / 64;
-
-// The same sum of at most kFinishThreads partials, by a block of kBlock
-// threads, on every thread: a kernel that needs a sum of few partials takes
-// it itself, in each of its blocks, instead of waiting for a launch of its
-// own (3 to 4 us, of about 100 us a CG step on small systems).  sh:
-// kFinishWaves doubles.
-__device__ __forceinline__ double finish_block(const double* partial, int nb, double* sh) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < kFinishThreads / kBlock; ++j) {
-        const int t = (int)threadIdx.x + j * kBlock;
-        double v = 0.0;
-        if (t < nb) v += partial[t];
-        v = wave_sum(v);
-        if (lane == 0) sh[w + j * (kBlock / 64)] = v;
-    }
-    __syncthreads();
-    double t = sh[0];
-    for (int k = 1; k < kFinishWaves; ++k) t += sh[k];
-    __syncthreads();
-    return t;
 }
 
 struct CgDirArgs {
