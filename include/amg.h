@@ -173,7 +173,7 @@ amg_status amg_pcg_solve(amg_hierarchy* h, const double* b, double* x, double to
  * device memory during a solve (tight serving loops, harnesses that forbid
  * it, work ordered among captured graphs).  The same preconditioned CG with
  * the same kernels and stopping rule, launched directly on hip_stream (no
- * captured graphs, no solve stream of the library): results are bitwise
+ * solve stream of the library): results are bitwise
  * those of amg_pcg_solve with device pointers.
  *
  * b, x   FP64 [n] device pointers of the current device; x holds the initial

@@ -45,10 +45,8 @@ struct Hierarchy {
     double* hscal = nullptr; // pinned host mirror of scal, and behind it the step it holds
     unsigned* hstep() const { return reinterpret_cast<unsigned*>(hscal + S_NSCAL); }
     unsigned steps = 0;      // steps asked to report so far
-    hipStream_t ws = nullptr;        // the solve's own stream (graphs cannot capture the null stream)
+    hipStream_t ws = nullptr;        // the solve's own stream
     hipEvent_t ev_in = nullptr;      // orders the solve after the caller's stream
-    hipGraphExec_t graph[2] = {nullptr, nullptr};  // captured CG steps, by parity
-    bool use_graphs = true;
     double t_setup = 0.0;
     double t_update = 0.0;   // duration of the last update_values
     bool fp32 = false;
@@ -63,7 +61,6 @@ struct Hierarchy {
     FirstStep<T> first_step();
     double vcycle_alg_bytes() const;
     double time_smoother(int level, int reps, hipStream_t s, double* bytes_per_launch);
-    hipGraphExec_t step_graph(const struct PcgWork& w, int cur);
     void first_smooth(const double* r, hipStream_t s);
     void ensure_solve_resources();
     void release_setup_data();
@@ -86,11 +83,10 @@ amg_status pcg_solve(Hierarchy& h, const double* b, double* x, double tol, int m
 
 // Workspace of one PCG solve: the iterate x (in/out) and r, z, p, q
 // (device vectors of the finest size), the device scalars (S_NSCAL), the
-// reduction partials and counter, a host mirror of the scalars, the stream,
-// and whether the captured step graphs may run (only with the hierarchy's
-// own buffers, which they hold).  With partial2 the steps leave short sums to
-// the kernels that need them, take the next V-cycle's first smoother step and
-// report their scalars into the hierarchy's pinned memory.
+// reduction partials and counter, a host mirror of the scalars and the stream.
+// With partial2 the steps leave short sums to the kernels that need them, take
+// the next V-cycle's first smoother step, report their scalars into the
+// hierarchy's pinned memory, and the V-cycle runs ahead of the test.
 struct PcgWork {
     double *x, *r, *z, *p, *q;
     double* scal;
@@ -98,7 +94,6 @@ struct PcgWork {
     unsigned* counter;
     double* hscal;
     hipStream_t stream;
-    bool graphs;
     double* partial2;
 };
 // the PCG iteration of pcg_solve on a given workspace; allocates nothing

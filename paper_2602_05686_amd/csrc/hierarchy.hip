@@ -211,8 +211,6 @@ struct Vec<float> {
 
 Hierarchy::~Hierarchy() {
     if (hscal) (void)hipHostFree(hscal);
-    for (auto& g : graph)
-        if (g) (void)hipGraphExecDestroy(g);
     if (ev_in) (void)hipEventDestroy(ev_in);
     give_stream(ws);  // back to the library's free list (its work stays ordered before later use)
 }
@@ -502,12 +500,6 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
     h.counter.alloc(2, mc);
     zero_async(h.counter.get(), 2 * sizeof(unsigned), s);
     zero_async(h.scal.get(), sizeof(double) * S_NSCAL, s);
-    {
-        // MATAMG_NO_GRAPH=1 runs every CG step eagerly (used to check the
-        // captured graphs against direct launches)
-        const char* ng = std::getenv("MATAMG_NO_GRAPH");
-        h.use_graphs = !(ng && ng[0] == '1');
-    }
     DBuf<int> flag(1, mc);
     zero_async(flag.get(), sizeof(int), s);
 
@@ -786,12 +778,6 @@ void update_values(Hierarchy& h, const double* val, bool host_ptrs, hipStream_t 
         coarse_inverse_check(h, cflag.get(), s);
     }
     if (h.fp32) cast_fp32(h, s);
-    // the captured CG steps hold the old smoother coefficients as kernel arguments
-    for (auto& g : h.graph)
-        if (g) {
-            (void)hipGraphExecDestroy(g);
-            g = nullptr;
-        }
     MATAMG_HIP(hipStreamSynchronize(s));
     h.t_update = now_s() - t0;
 }
@@ -927,19 +913,24 @@ double Hierarchy::vcycle_alg_bytes() const {
 // ---------------------------------------------------------------------- PCG
 namespace {
 
-// One CG step: z = M r, p = z + beta p (old < 0: p = z), q = A p, and x, r
-// updated, with the scalars in slots nxt (this step's r.z) and old.
-// first_done: the step before has taken the V-cycle's first smoother step.
-void cg_step(Hierarchy& h, const PcgWork& w, int nxt, int old, bool first_done) {
+// A CG step is z = M r with r.z, and then p = z + beta p (first: p = z), q = A p,
+// and x, r updated.  The scalars are in the slots nxt (this step's r.z) and
+// old.  first_done: the step before has taken the V-cycle's first smoother step.
+bool own_sums(const Hierarchy& h, const PcgWork& w) {
+    return w.partial2 && h.nlev > 1 && stream_partials(h.lev[0].A) <= kOwnSumPartials;
+}
+void cg_precondition(Hierarchy& h, const PcgWork& w, int nxt, bool first_done) {
+    h.vcycle(w.r, w.z, DotTarget{w.partial, w.counter, own_sums(h, w) ? nullptr : w.scal + nxt}, w.stream, first_done);
+}
+void cg_advance(Hierarchy& h, const PcgWork& w, int nxt, int old, bool first) {
     const DCsr& A = h.lev[0].A;
     const int n = A.n;
     hipStream_t s = w.stream;
     auto dt = [&](int slot) { return DotTarget{w.partial, w.counter, w.scal + slot}; };
     const int nb = stream_partials(A);
-    const bool own = w.partial2 && h.nlev > 1 && nb <= kOwnSumPartials;
+    const bool own = own_sums(h, w);
     const DotTarget left{w.partial, w.counter, nullptr};
-    h.vcycle(w.r, w.z, own ? left : dt(nxt), s, first_done);
-    cg_direction(n, w.p, w.z, w.scal + nxt, old >= 0 ? w.scal + old : nullptr, own ? left : DotTarget{}, nb, s);
+    cg_direction(n, w.p, w.z, w.scal + nxt, first ? nullptr : w.scal + old, own ? left : DotTarget{}, nb, s);
     spmv_dot(A, w.p, w.q, own ? left : dt(S_PQ), s);
     auto update = [&](auto tag) {
         using T = decltype(tag);
@@ -952,8 +943,9 @@ void cg_step(Hierarchy& h, const PcgWork& w, int nxt, int old, bool first_done) 
     };
     if (h.fp32) update(float{});
     else update(double{});
+    // reported, and this step's r.z kept as the next one's old
     if (w.partial2)
-        finish_report(DotTarget{w.partial2, w.counter, w.scal + S_RR}, vector_partials(n), w.scal, S_NSCAL,
+        finish_report(DotTarget{w.partial2, w.counter, w.scal + S_RR}, vector_partials(n), w.scal, S_NSCAL, nxt, old,
                       h.counter.get() + 1, h.hscal, h.hstep(), s);
 }
 
@@ -977,26 +969,6 @@ void wait_report(Hierarchy& h, hipStream_t s) {
 
 }  // namespace
 
-// One captured graph per parity of the iteration counter: one CG step.  All
-// operands are hierarchy-owned buffers, so the two graphs are captured once
-// per hierarchy and replayed every step; the convergence test reads the
-// scalars after each replay.
-hipGraphExec_t Hierarchy::step_graph(const PcgWork& w, int cur) {
-    const int g = (cur == S_RZ0) ? 0 : 1;
-    if (graph[g]) return graph[g];
-    const int nxt = (cur == S_RZ0) ? S_RZ1 : S_RZ0;
-    MATAMG_HIP(hipStreamBeginCapture(ws, hipStreamCaptureModeThreadLocal));
-    cg_step(*this, w, nxt, cur, nlev > 1);
-    hipGraph_t gr = nullptr;
-    MATAMG_HIP(hipStreamEndCapture(ws, &gr));
-    hipGraphExec_t ex = nullptr;
-    const hipError_t e = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(gr);
-    MATAMG_HIP(e);
-    graph[g] = ex;
-    return ex;
-}
-
 // the widest fused reduction of a solve: the finest operator's streaming
 // launches (q = A p, residual norms, the last smoothing step's r.z) and the
 // vector kernels' grids
@@ -1006,6 +978,10 @@ size_t pcg_partials(const Hierarchy& h) {
 
 // The PCG iteration on an explicit workspace (see PcgWork): the convergence
 // test reads the device scalars after every step through w.hscal.
+// the part of the foreseen residual that has to be above the tolerance for
+// the next V-cycle to be launched ahead
+constexpr double kAheadMargin = 0.5;
+
 amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, int max_iter, int* iters_out,
                    double* rel_out) {
     const DCsr& A = h.lev[0].A;
@@ -1036,11 +1012,30 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
         rel_true = std::sqrt(w.hscal[S_RR]) / bn;
         st = AMG_OK;
     } else if (max_iter > 0) {
-        // first step eagerly: z = M r, p = z, q = A p, x and r updated
-        int cur = S_RZ0;
+        // Steps that report keep r.z in S_RZ1 and the one before in S_RZ0;
+        // the others (their scalars read back) take the two slots in turn.
         const bool fused = w.partial2 && h.nlev > 1;  // a step takes the next one's first smoother step
-        cg_step(h, w, cur, -1, false);
-        if (w.partial2) ++h.steps;
+        int cur = w.partial2 ? S_RZ1 : S_RZ0, old = w.partial2 ? S_RZ0 : S_RZ1;
+        // The next step's V-cycle changes nothing that the test of this step
+        // or a stop reads (z and work vectors only), so it goes out with this
+        // step wherever the test is not about to end the solve, and the host's
+        // wait and launches pass beside it.  Where the residual falls faster
+        // than foreseen, one V-cycle is for nothing.  Launched kernel by
+        // kernel: a graph a step keeps the GPU idle for 4 to 6 us between two
+        // replays (37x23x29 anisotropic, 46 steps: 4.67 ms with one graph a
+        // step waited for, 4.63 ms with the V-cycle ahead in it, 4.46 ms in
+        // launches; 64^2 checkerboard 1.83, 1.79 and 1.78 ms) and has to be
+        // captured once, 0.1 to 0.2 ms.
+        double last = std::sqrt(w.hscal[S_RR]) / bn, rate = 0.1;
+        bool ahead = false;
+        auto step = [&](int it) {
+            if (!ahead) cg_precondition(h, w, cur, fused && it > 1);
+            ahead = w.partial2 && it < max_iter && last * rate * kAheadMargin > tol;
+            cg_advance(h, w, cur, old, it == 1);
+            if (ahead) cg_precondition(h, w, cur, fused);
+            if (w.partial2) ++h.steps;
+        };
+        step(1);
         for (int it = 1;; ++it) {
             if (w.partial2) wait_report(h, ws);
             else read_scal();
@@ -1063,13 +1058,13 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
                 // residual replacement, and the first smoother step from it
                 MATAMG_HIP(hipMemcpyAsync(r, q, sizeof(double) * n, hipMemcpyDeviceToDevice, ws));
                 if (fused && it < max_iter) h.first_smooth(r, ws);
+                ahead = false;
             }
             if (it >= max_iter) break;
-            const int nxt = (cur == S_RZ0) ? S_RZ1 : S_RZ0;
-            if (w.graphs) MATAMG_HIP(hipGraphLaunch(h.step_graph(w, cur), ws));
-            else cg_step(h, w, nxt, cur, fused);
-            if (w.partial2) ++h.steps;
-            cur = nxt;
+            rate = std::min(rel / last, 1.0);
+            last = rel;
+            if (!w.partial2) std::swap(cur, old);
+            step(it + 1);
         }
     }
     *iters_out = iters;
@@ -1097,9 +1092,8 @@ amg_status pcg_solve(Hierarchy& h, const double* b_in, double* x_io, double tol,
     } else {
         MATAMG_HIP(hipMemcpyAsync(x, x_io, sizeof(double) * n, hipMemcpyDeviceToDevice, ws));
     }
-    // the captured step graphs hold these buffers
     PcgWork w{x, h.cr.get(), h.cz.get(), h.cp.get(), h.cq.get(), h.scal.get(), h.partial.get(), h.counter.get(),
-              h.hscal, ws, h.use_graphs, h.partial2.get()};
+              h.hscal, ws, h.partial2.get()};
     int iters = 0;
     double rel_true = 0.0;
     const amg_status st = pcg_run(h, w, b, tol, max_iter, &iters, &rel_true);

@@ -418,9 +418,10 @@ __global__ __launch_bounds__(kBlock) void k_cg_direction(CgDirArgs a) {
 }
 
 // finish_body, and then the solve's scalars to the host's copy (pinned
-// memory), its step number last
-__global__ __launch_bounds__(kFinishThreads) void k_finish_report(FinishArgs a, const double* scal, int words,
-                                                                  unsigned* step, double* host, unsigned* host_step) {
+// memory), its step number last, and slot `from` to slot `to`
+__global__ __launch_bounds__(kFinishThreads) void k_finish_report(FinishArgs a, double* scal, int words, int from,
+                                                                  int to, unsigned* step, double* host,
+                                                                  unsigned* host_step) {
     __shared__ double sh[kFinishThreads / 64];
     finish_body(a, sh);
     if (threadIdx.x == 0) {
@@ -428,6 +429,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish_report(FinishArgs a, 
         const unsigned s = *step + 1u;
         *step = s;
         __hip_atomic_store(host_step, s, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        scal[to] = scal[from];
     }
 }
 
@@ -500,10 +502,10 @@ void cg_direction(int64_t n, double* p, const double* z, double* rz_new, const d
 
 int vector_partials(int64_t n) { return vec_grid(n); }
 
-void finish_report(const DotTarget& dt, int nblocks, const double* scal, int words, unsigned* step, double* host,
-                   unsigned* host_step, hipStream_t s) {
+void finish_report(const DotTarget& dt, int nblocks, double* scal, int words, int from, int to, unsigned* step,
+                   double* host, unsigned* host_step, hipStream_t s) {
     hipLaunchKernelGGL(k_finish_report, dim3(1), dim3(kFinishThreads), 0, s,
-                       FinishArgs{nblocks, dt.partial, dt.result}, scal, words, step, host, host_step);
+                       FinishArgs{nblocks, dt.partial, dt.result}, scal, words, from, to, step, host, host_step);
     MATAMG_LAUNCH_CHECK();
 }
 

@@ -111,9 +111,9 @@ void cg_direction(int64_t n, double* p, const double* z, double* rz_new, const d
                   int rz_blocks, hipStream_t s);
 int vector_partials(int64_t n);
 // finish_sum, then `words` of scal to host memory (pinned), then *step + 1 to
-// *step and *host_step
-void finish_report(const DotTarget& dt, int nblocks, const double* scal, int words, unsigned* step, double* host,
-                   unsigned* host_step, hipStream_t s);
+// *step and *host_step, and scal[from] to scal[to]
+void finish_report(const DotTarget& dt, int nblocks, double* scal, int words, int from, int to, unsigned* step,
+                   double* host, unsigned* host_step, hipStream_t s);
 template <typename A, typename B>
 void cast_vec(int64_t n, const A* in, B* out, hipStream_t s);
 // seeded values in (-1, 1) and sum_i v_i^2 as dot(v, v) takes it; its number

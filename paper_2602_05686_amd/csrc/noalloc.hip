@@ -1,8 +1,8 @@
 // The allocation-free PCG solve: amg_pcg_solve's iteration with its
 // workspace (the CG vectors r, z, p, q, the device scalars and the reduction
 // partials) in one file-scope device array instead of hierarchy buffers, on
-// the caller's stream, without captured graphs, solve stream, event or
-// pinned mirror, so that the call allocates nothing.
+// the caller's stream, without solve stream, event or pinned mirror, so that
+// the call allocates nothing.
 #include <chrono>
 #include <mutex>
 
@@ -79,7 +79,7 @@ amg_status pcg_solve_noalloc(Hierarchy& h, const double* b, double* x, double to
     zero_async(scal, sizeof(double) * S_NSCAL, s);
     zero_async(counter, sizeof(unsigned), s);
     double hscal[S_NSCAL] = {};
-    PcgWork w{x, r, z, p, q, scal, partial, counter, hscal, s, false, nullptr};
+    PcgWork w{x, r, z, p, q, scal, partial, counter, hscal, s, nullptr};
     int iters = 0;
     double rel_true = 0.0;
     const amg_status st = pcg_run(h, w, b, tol, max_iter, &iters, &rel_true);
