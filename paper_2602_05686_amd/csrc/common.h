@@ -178,6 +178,9 @@ class DBuf {
 // distinct-column runs kept per streaming block (see DCsr::urun)
 constexpr int kMaxRuns = 6;
 constexpr int kRunWords = kMaxRuns + 2;
+// windows of 2^16 columns kept per streaming block (see DCsr::uwin)
+constexpr int kMaxWin = 4;
+constexpr int kWinWords = 12;
 
 // windows of columns kept per row-dictionary group (see DCsr::drun)
 constexpr int kDictRuns = 8;
@@ -217,6 +220,14 @@ struct DCsr {
     // columns keep the runs instead of a list: urun[kRunWords b ..] = {runs,
     // distinct columns, then start | length << 16 per run}; runs = 0: none
     DBuf<uint32_t> urun;
+    // Where some block's columns span 2^16 values or more, a record per block
+    // instead of cbase and urun: uwin[kWinWords b ..] = {distinct columns
+    // listed (0: none), windows, base, then the list index where the next
+    // window starts and its base, up to kMaxWin}.  A listed block's uoff are
+    // offsets from the base of their window; without a list, one window: col =
+    // base + col16; no window: the block's col16 are not used (col instead).
+    DBuf<int> uwin;
+    int64_t npacked = 0;  // entries in blocks with windows
     // row dictionaries (k_rows.hip), or empty: groups of dk consecutive row
     // blocks store each distinct row (values and column offsets from the row)
     // once.  Row r's is drow_of[r] of its group g's records in dinfo, each
@@ -248,10 +259,13 @@ struct DCsr {
         return (double)nnz * (size + col_bytes()) + 4.0 * (n + 1) + (col16 ? 4.0 * nblk : 0.0) + unique_bytes();
     }
     // column bytes per stored entry the streaming kernels read
-    double col_bytes() const { return col16 ? 2.0 : 4.0; }
+    double col_bytes() const {
+        return uwin ? 4.0 - 2.0 * (double)npacked / (double)nnz : col16 ? 2.0 : 4.0;
+    }
     // bytes of the distinct-column lists and their block table
     double unique_bytes() const {
-        return (ustart ? 2.0 * (double)nuniq + 4.0 * (nblk + 1) : 0.0) + (urun ? 4.0 * kRunWords * nblk : 0.0);
+        return (ustart ? 2.0 * (double)nuniq + 4.0 * (nblk + 1) : 0.0) + (urun ? 4.0 * kRunWords * nblk : 0.0) +
+               (uwin ? 4.0 * kWinWords * nblk : 0.0);
     }
 };
 

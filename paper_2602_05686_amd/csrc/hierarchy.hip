@@ -67,7 +67,7 @@ int wide_block_min(int level, bool fp32) {
 }
 
 void widen_stream_blocks(DCsr& A, int min_blocks, MemCounter* mc, hipStream_t s) {
-    if (A.group != 1 || !A.col16 || A.cap != kStreamCap || A.nblk < min_blocks) return;
+    if (A.group != 1 || !A.col16 || A.uwin || A.cap != kStreamCap || A.nblk < min_blocks) return;
     DBuf<int> blk = std::move(A.blk), blkk = std::move(A.blkk), cbase = std::move(A.cbase),
               ustart = std::move(A.ustart);
     DBuf<uint16_t> col16 = std::move(A.col16), uoff = std::move(A.uoff);

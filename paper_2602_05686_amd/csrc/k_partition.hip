@@ -352,6 +352,122 @@ __global__ __launch_bounds__(kBlock) void k_block_uniques_fill(int nblk, const i
     }
 }
 
+// Per block of a matrix that has blocks whose columns span 2^16 values or
+// more: its record in uwin (see DCsr::uwin).  The block's columns are sorted in
+// LDS; the distinct ones, where they are staged (the rule of
+// k_block_uniques_count), are covered by windows of 2^16 columns from the first
+// on -- a mesh row gathers from a few planes, so a few windows do -- and the
+// entries' col16 become their places in the list.  The list goes to
+// off[blkk[b] ..], its length to ucnt[b]; *packed counts the entries of blocks
+// with windows.
+__global__ __launch_bounds__(kBlock) void k_block_windows(int nblk, const int* blk, const int* blkk, const int* col,
+                                                          int group, uint16_t* col16, uint16_t* off, int* ucnt,
+                                                          int* uwin, int* packed) {
+    constexpr int kNone = 0x7fffffff;
+    constexpr int kPer = kStreamCap / kBlock;
+    __shared__ int keys[kStreamCap];
+    __shared__ int red[kBlock / 64];
+    __shared__ int rec[kWinWords];
+    for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
+        const int r0 = blk[b], r1 = blk[b + 1], k0 = blkk[b], cnt = blkk[b + 1] - k0;
+        if (threadIdx.x < kWinWords) rec[threadIdx.x] = 0;
+        const bool skip = cnt <= 0 || long_row_block(r0, r1, k0, k0 + cnt, group);
+        int nu = 0;
+        if (!skip) {
+            int size = kBlock;
+            while (size < cnt) size *= 2;
+            for (int i = threadIdx.x; i < size; i += kBlock) keys[i] = i < cnt ? col[k0 + i] : kNone;
+            __syncthreads();
+            for (int run = 2; run <= size; run *= 2)
+                for (int d = run / 2; d > 0; d /= 2) {
+                    for (int i = threadIdx.x; i < size / 2; i += kBlock) {
+                        const int p = 2 * i - (i & (d - 1));
+                        const int x = keys[p], y = keys[p + d];
+                        if ((x > y) == ((p & run) == 0)) {
+                            keys[p] = y;
+                            keys[p + d] = x;
+                        }
+                    }
+                    __syncthreads();
+                }
+            // the distinct ones to the front
+            const int per = size / kBlock, e0 = (int)threadIdx.x * per;
+            int v[kPer], mine = 0;
+            int before = e0 > 0 ? keys[e0 - 1] : -1;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                v[i] = i < per ? keys[e0 + i] : kNone;
+                if (v[i] == before) v[i] = kNone;
+                else before = v[i];
+                mine += v[i] != kNone;
+            }
+            int at = block_exclusive(mine, red, &nu);  // (all have read before any writes)
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                if (v[i] != kNone) keys[at++] = v[i];
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                int w = 0;
+                for (int j = 0; j < nu;) {
+                    if (w == kMaxWin) {
+                        w = 0;
+                        break;
+                    }
+                    if (w > 0) rec[1 + 2 * w] = j;
+                    rec[2 + 2 * w] = keys[j];
+                    const int last = keys[j] > kNone - 0xffff ? kNone : keys[j] + 0xffff;
+                    ++w;
+                    int lo = j + 1, hi = nu;  // the first beyond the window
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (keys[mid] <= last) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    j = lo;
+                }
+                const bool staged = w > 0 && nu <= unique_cap(kStreamCap) && nu * 100 <= kUniqueReusePct * cnt;
+                rec[0] = staged ? nu : 0;
+                rec[1] = staged || w == 1 ? w : 0;
+                if (rec[1] > 0) atomicAdd(packed, cnt);
+            }
+        }
+        __syncthreads();
+        const int listed = rec[0], windows = rec[1];
+        if (listed > 0) {
+            for (int k = threadIdx.x; k < cnt; k += kBlock) {
+                const int c = col[k0 + k];
+                int lo = 0, hi = nu - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (keys[mid] < c) lo = mid + 1;
+                    else hi = mid;
+                }
+                col16[k0 + k] = (uint16_t)lo;
+            }
+            for (int j = threadIdx.x; j < nu; j += kBlock) {
+                int base = rec[2];
+                for (int w = 1; w < windows; ++w)
+                    if (j >= rec[1 + 2 * w]) base = rec[2 + 2 * w];
+                off[k0 + j] = (uint16_t)(keys[j] - base);
+            }
+        } else if (windows > 0) {
+            for (int k = threadIdx.x; k < cnt; k += kBlock) col16[k0 + k] = (uint16_t)(col[k0 + k] - rec[2]);
+        }
+        if (threadIdx.x < kWinWords) uwin[(size_t)b * kWinWords + threadIdx.x] = rec[threadIdx.x];
+        if (threadIdx.x == 0) ucnt[b] = listed;
+        __syncthreads();
+    }
+}
+
+// the lists of k_block_windows, one after the other
+__global__ __launch_bounds__(kBlock) void k_copy_lists(int nblk, const int* blkk, const int* ustart,
+                                                       const uint16_t* off, uint16_t* uoff) {
+    for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
+        const int k0 = blkk[b], u0 = ustart[b], nu = ustart[b + 1] - u0;
+        for (int j = threadIdx.x; j < nu; j += kBlock) uoff[u0 + j] = off[k0 + j];
+    }
+}
+
 // blkk[b] = rp[blk[b]] for b <= nblk
 __global__ void k_block_entries(int nblk, const int* rp, const int* blk, int* blkk) {
     FOR_ROWS(b, (int64_t)nblk + 1) blkk[b] = rp[blk[b]];
@@ -366,6 +482,8 @@ void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap
     A.ustart.release();
     A.uoff.release();
     A.urun.release();
+    A.uwin.release();
+    A.npacked = 0;
     A.nuniq = 0;
     A.sblk.release();
     A.snblk = 0;
@@ -445,7 +563,47 @@ void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap
                            (const int*)A.blk.get(), (const int*)A.cbase.get(), A.col16.get());
         MATAMG_LAUNCH_CHECK();
         block_uniques(A, mc, s);
+    } else if (pack && A.nnz > 0 && cap == kStreamCap) {
+        block_windows(A, mc, s);
     }
+}
+
+// Packed columns by windows, for a matrix that one base per block cannot pack
+// (one block is enough: a ring's first and last rows, an uneven level of a large
+// stack).  It then reads 2 bytes of column an entry, not 4, and gathers through
+// LDS: FP64 smoother of the 80x600x4 annulus 18.5 -> 15.0 us, of the 96^3
+// cube's level 2 27 -> 22 us, of the 192^3 stack's levels 1 to 3 323, 256 and
+// 178 -> 311, 226 and 165 us.  A matrix most of whose entries are in blocks
+// without windows would gain little and stays as it is.
+void block_windows(DCsr& A, MemCounter* mc, hipStream_t s) {
+    const int nblk = A.nblk;
+    if (nblk <= 0) return;
+    DBuf<int> cnt((size_t)nblk, mc), tmp(scan_tmp_size(nblk), mc);
+    DBuf<uint16_t> off((size_t)A.nnz, mc);
+    A.col16.alloc((size_t)A.nnz, mc);
+    A.uwin.alloc((size_t)nblk * kWinWords, mc);
+    A.ustart.alloc((size_t)nblk + 2, mc);  // (the number of packed entries behind the starts)
+    zero_async(A.ustart.get() + nblk + 1, sizeof(int), s);
+    hipLaunchKernelGGL(k_block_windows, dim3(std::min(nblk, 16384)), dim3(kBlock), 0, s, nblk, (const int*)A.blk.get(),
+                       (const int*)A.blkk.get(), (const int*)A.col.get(), A.group, A.col16.get(), off.get(), cnt.get(),
+                       A.uwin.get(), A.ustart.get() + nblk + 1);
+    MATAMG_LAUNCH_CHECK();
+    exclusive_scan(cnt.get(), A.ustart.get(), nblk, tmp.get(), s);
+    int res[2] = {0, 0};  // list length, packed entries
+    d2h(res, A.ustart.get() + nblk, 2, s);
+    if (2 * (int64_t)res[1] < A.nnz) {
+        A.col16.release();
+        A.uwin.release();
+        A.ustart.release();
+        return;
+    }
+    A.npacked = res[1];
+    A.nuniq = res[0];
+    A.uoff.alloc((size_t)(res[0] > 0 ? res[0] : 1), mc);
+    if (res[0] > 0)
+        hipLaunchKernelGGL(k_copy_lists, dim3(std::min(nblk, 16384)), dim3(kBlock), 0, s, nblk, (const int*)A.blkk.get(),
+                           (const int*)A.ustart.get(), (const uint16_t*)off.get(), A.uoff.get());
+    MATAMG_LAUNCH_CHECK();
 }
 
 void block_uniques(DCsr& A, MemCounter* mc, hipStream_t s) {

@@ -302,6 +302,7 @@ SArgs<T> base_args(const DCsr& A, const T* val, const T* x) {
     a.ustart = A.ustart.get();
     a.uoff = A.uoff.get();
     a.urun = A.urun.get();
+    a.uwin = A.uwin.get();
     a.x = x;
     dict_args(A, a);
     return a;

@@ -33,6 +33,9 @@ int stream_group(const int* rowptr_host, int n);
 void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap = kStreamCap);
 // the distinct-column lists of A's packed streaming blocks (see DCsr::ustart)
 void block_uniques(DCsr& A, MemCounter* mc, hipStream_t s);
+// the column windows of A's streaming blocks (see DCsr::uwin), where some span
+// 2^16 values or more
+void block_windows(DCsr& A, MemCounter* mc, hipStream_t s);
 
 // the row dictionaries of A (see DCsr::drow_of) where its rows repeat; none
 // otherwise.  Synchronises s.

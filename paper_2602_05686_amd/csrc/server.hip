@@ -77,6 +77,7 @@ SArgs<T> sargs(const DCsr& M, const T* val, const T* x) {
     a.ustart = M.ustart.get();
     a.uoff = M.uoff.get();
     a.urun = M.urun.get();
+    a.uwin = M.uwin.get();
     a.x = x;
     dict_args(M, a);
     return a;

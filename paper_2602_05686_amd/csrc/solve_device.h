@@ -40,6 +40,7 @@ struct SArgs {
     const int* ustart;       // packed blocks' distinct-column lists (or null):
     const uint16_t* uoff;    // block b's are uoff[ustart[b] .. ustart[b+1])
     const uint32_t* urun;    // or their runs (DCsr::urun; null: none)
+    const int* uwin;         // or their windows (DCsr::uwin; null: none)
     const T* x;        // gathered operand
     const T* b;        // right-hand side (RESID, SMOOTH, RESNORM); SCALENORM: partial sums of x.x
     const T* yin;      // ADD: base vector; SMOOTH: iterate at the row
@@ -204,10 +205,12 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ int stage_head(int k0, int cnt) { return cnt > 0 ? (k0 & 1) : 0; }
 
-template <typename T, int MODE, int NP, int UQ>
+template <typename T, int MODE, int NP, int UQ, bool WIN>
 __device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, int cnt, T scale, T* prod) {
     using P2 = typename PairOf<T>::type;
-    const int base = a.cbase[bid];
+    // (only a matrix with no windows takes the cap of wide blocks)
+    const int* win = WIN && a.uwin ? a.uwin + (size_t)bid * kWinWords : nullptr;
+    const int base = win ? win[2] : a.cbase[bid];
     const int head = stage_head(k0, cnt);  // entry 0 alone when the block starts at an odd position
     const int body = cnt - head;
     const int np = body >> 1;  // whole pairs from the even position k0 + head
@@ -215,10 +218,10 @@ __device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, 
     const int tid = (int)threadIdx.x;
     // the block's distinct columns (block-uniform): runs, a list, or none
     // (gathers)
-    const uint32_t* rec = a.urun ? a.urun + (size_t)bid * kRunWords : nullptr;
+    const uint32_t* rec = a.urun && !win ? a.urun + (size_t)bid * kRunWords : nullptr;
     const int nruns = rec ? (int)rec[0] : 0;
     const int u0 = a.ustart ? a.ustart[bid] : 0;
-    const int nu = nruns > 0 ? (int)rec[1] : (a.ustart ? a.ustart[bid + 1] - u0 : 0);
+    const int nu = win ? win[0] : nruns > 0 ? (int)rec[1] : (a.ustart ? a.ustart[bid + 1] - u0 : 0);
     u16x2 c[NP > 0 ? NP : 1];
     P2 v[NP > 0 ? NP : 1];
 #pragma unroll
@@ -270,6 +273,18 @@ __device__ __forceinline__ void stage_pairs(const SArgs<T>& a, int bid, int k0, 
             for (int q = 0; q < UQ; ++q) {
                 const int j = tid + q * kBlock;
                 off[q] = (int)a.uoff[u0 + (j < nu ? j : nu - 1)];
+            }
+            if (win && win[1] > 1) {
+                // several windows: each list index takes its own one's base
+#pragma unroll
+                for (int q = 0; q < UQ; ++q) {
+                    const int j = min(tid + q * kBlock, nu - 1);
+                    int b = base;
+#pragma unroll
+                    for (int w = 1; w < kMaxWin; ++w)
+                        if (w < win[1] && j >= win[1 + 2 * w]) b = win[2 + 2 * w];
+                    off[q] += b - base;
+                }
             }
         }
         T xv[UQ > 0 ? UQ : 1];
@@ -393,21 +408,23 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         // from packed or plain columns (uniform per matrix)
         const int nu = (cnt + kBlock - 1) / kBlock;
         constexpr int kUQ = unique_cap(CAP) / kBlock;  // distinct values per thread
-        if (a.col16) {
+        constexpr bool kWin = CAP == kStreamCap;
+        const bool packed = a.col16 && !(kWin && a.uwin && a.uwin[(size_t)bid * kWinWords + 1] == 0);
+        if (packed) {
             // pairs of entries: ceil(pairs / kBlock) strides (block-uniform)
             switch (((cnt - stage_head(k0, cnt)) / 2 + kBlock - 1) / kBlock) {
-                case 0: stage_pairs<T, MODE, 0, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                case 1: stage_pairs<T, MODE, 1, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                case 2: stage_pairs<T, MODE, 2, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                case 3: stage_pairs<T, MODE, 3, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                case 4: stage_pairs<T, MODE, 4, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                case 0: stage_pairs<T, MODE, 0, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                case 1: stage_pairs<T, MODE, 1, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                case 2: stage_pairs<T, MODE, 2, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                case 3: stage_pairs<T, MODE, 3, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                case 4: stage_pairs<T, MODE, 4, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
                 default:
                     if constexpr (CAP > kStreamCap) {
                         switch (((cnt - stage_head(k0, cnt)) / 2 + kBlock - 1) / kBlock) {
-                            case 5: stage_pairs<T, MODE, 5, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                            case 6: stage_pairs<T, MODE, 6, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                            case 7: stage_pairs<T, MODE, 7, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
-                            case 8: stage_pairs<T, MODE, 8, kUQ>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 5: stage_pairs<T, MODE, 5, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 6: stage_pairs<T, MODE, 6, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 7: stage_pairs<T, MODE, 7, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
+                            case 8: stage_pairs<T, MODE, 8, kUQ, kWin>(a, bid, k0, cnt, scale, S.prod); break;
                             default: break;
                         }
                     }
@@ -475,8 +492,8 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         // flight together.  A long row's block is never staged, so packed
         // columns hold plain offsets from the block's base.
         T s = 0;
-        const int* col = a.col16 ? nullptr : a.col;
-        const int base = a.col16 ? a.cbase[bid] : 0;
+        const int* col = a.col16 && !a.uwin ? nullptr : a.col;
+        const int base = col ? 0 : a.cbase[bid];
         int t = (int)threadIdx.x;
         for (; t + 3 * kBlock < cnt; t += 4 * kBlock) {
             int c[4];
