@@ -4,13 +4,17 @@
 // The partition is the greedy one: walking the rows in order, a block takes
 // rows while it holds fewer than max_block_rows(G) rows and its stored
 // entries stay within the cap (kStreamCap, or kStreamCapWide); a row longer
-// than long_row_limit(G) forms a
-// block of its own.  The walk is sequential, but the block that starts at row r ends at a
-// row next(r) that depends on r alone, so every next(r) is computed in
-// parallel (binary searches over the row pointer and the list of long rows)
-// and the block starts -- the orbit of row 0 under next -- are marked by
-// radix-8 pointer jumping: after round k every start within 8^(k+1) blocks
-// of row 0 is marked.  The result equals the host walk exactly.
+// than long_row_limit(G) forms a block of its own.  The walk is sequential,
+// but the block that starts at row r ends at a row that depends on r alone, so
+// every row's step is computed in parallel, and a walk enters a chunk of rows
+// at one of its first 256: each chunk is walked from all of them at once, the
+// chunks' entries then follow one from the other, and each chunk is walked
+// once more, from its own entry, for the starts.  The result equals the host
+// walk exactly.  Launches are what bounds it on small matrices and memory
+// passes on large ones: five launches, three for a single chunk (radix-8
+// pointer jumping over marks, with scans, took about twenty, and the setup of the
+// 128^2 two-domain problem 5.6 ms, now 4.2 ms; of the 128^3 stack 34.8 and
+// 32.2 ms).
 #include <algorithm>
 
 #include "device_util.h"
@@ -26,17 +30,16 @@ inline int grid1(int64_t n) {
 
 #define FOR_ROWS(i, n) for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < (n); i += (int64_t)gridDim.x * kBlock)
 
-// longest row (out[0]) and the entries in rows wider than kWideRow (out[6]);
-// launched with a small grid so that few blocks meet at the atomics (both
-// results are order-independent)
-__global__ __launch_bounds__(kBlock) void k_max_row_len(int n, const int* rp, int* out) {
+// one bitmap of long rows for both group sizes, steps of a byte
+constexpr int kMaxStep = 256;
+static_assert(long_row_limit(1) == long_row_limit(8) && max_block_rows(1) <= kMaxStep && max_block_rows(8) <= kMaxStep);
+constexpr int kStatBlocks = 256;      // most workgroups of k_row_stats
+constexpr int kChunkTile = 16384;     // rows whose steps are in LDS at a time
+constexpr int kMaxChunks = 512;
+
+// sums (w) and maxima (m) over the block's threads, on every thread
+__device__ __forceinline__ void block_max_sum(int& m, int& w) {
     __shared__ int sm[kBlock / 64], sw[kBlock / 64];
-    int m = 0, w = 0;
-    FOR_ROWS(i, n) {
-        const int len = rp[i + 1] - rp[i];
-        m = max(m, len);
-        if (len > kWideRow) w += len;
-    }
     for (int off = 32; off > 0; off >>= 1) {
         m = max(m, __shfl_xor(m, off, 64));
         w += __shfl_xor(w, off, 64);
@@ -46,105 +49,159 @@ __global__ __launch_bounds__(kBlock) void k_max_row_len(int n, const int* rp, in
         sw[threadIdx.x >> 6] = w;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < kBlock / 64; ++k) {
-            m = max(m, sm[k]);
-            w += sw[k];
-        }
-        if (m > 0) atomicMax(out, m);
-        if (w > 0) atomicAdd(out + 6, w);
+    m = 0;
+    w = 0;
+    for (int k = 0; k < kBlock / 64; ++k) {
+        m = max(m, sm[k]);
+        w += sw[k];
     }
 }
 
-// par[0] = longest row, par[6] = entries in wide rows -> par[1] = threads per
-// row, par[2] = long-row limit, par[3] = most rows per block (the host's
-// stream_group rule)
-__global__ void k_group_params(int n, const int* rp, int* par) {
-    const int group = stream_group_rule(par[0], par[6], rp[n]);
-    par[1] = group;
-    par[2] = long_row_limit(group);
-    par[3] = max_block_rows(group);
+// part[block] = {longest row, entries in rows wider than kWideRow} of the
+// block's rows; bits: the rows that are long
+__global__ __launch_bounds__(kBlock) void k_row_stats(int n, const int* rp, int2* part, unsigned long long* bits) {
+    int m = 0, w = 0;
+    for (int64_t b = (int64_t)blockIdx.x * kBlock; b < n; b += (int64_t)gridDim.x * kBlock) {
+        const int64_t r = b + threadIdx.x;
+        const int len = r < n ? rp[r + 1] - rp[r] : 0;
+        const unsigned long long lw = __ballot(len > long_row_limit(1));
+        if ((threadIdx.x & 63) == 0) bits[r >> 6] = lw;
+        m = max(m, len);
+        if (len > kWideRow) w += len;
+    }
+    block_max_sum(m, w);
+    if (threadIdx.x == 0) part[blockIdx.x] = int2{m, w};
 }
 
-__global__ void k_long_flags(int n, const int* rp, const int* par, int* flags) {
-    const int limit = par[2];
-    FOR_ROWS(i, n) flags[i] = (rp[i + 1] - rp[i] > limit) ? 1 : 0;
-}
-
-__global__ void k_long_list(int n, const int* flags, const int* pos, int* list) {
-    FOR_ROWS(i, n) if (flags[i]) list[pos[i]] = (int)i;
-}
-
-// end (exclusive) of the block that starts at row r; next[n] = n
-__global__ void k_block_next(int n, const int* rp, const int* par, const int* longs, const int* nlong, int bcap,
-                             int* next) {
-    const int nl = *nlong;
-    const int limit = par[2], max_rows = par[3];
-    FOR_ROWS(r64, (int64_t)n + 1) {
+// step[r]: rows, less one, of the block that would start at row r;
+// par[1] = threads per row (the host's stream_group rule), par[2] = longest
+// row, par[3] = 0
+__global__ __launch_bounds__(kBlock) void k_row_steps(int n, const int* rp, const int2* part, int nparts,
+                                                      const unsigned long long* bits, int cap, uint8_t* step,
+                                                      int* par) {
+    int m = 0, w = 0;
+    if ((int)threadIdx.x < nparts) {
+        const int2 p = part[threadIdx.x];
+        m = p.x;
+        w = p.y;
+    }
+    block_max_sum(m, w);
+    const int group = stream_group_rule(m, w, rp[n]);
+    const int limit = long_row_limit(group), max_rows = max_block_rows(group);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        par[1] = group;
+        par[2] = m;
+        par[3] = 0;
+    }
+    FOR_ROWS(r64, n) {
         const int r = (int)r64;
-        if (r == n) {
-            next[r] = n;
-            continue;
+        const int first = rp[r];
+        int e = r + 1;
+        if (rp[r + 1] - first <= limit) {
+            // largest e with at most cap entries (e = r + 1 always has),
+            // then up to the first long row
+            int lo = r + 1, hi = min(n, r + max_rows);
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (rp[mid] - first <= cap) lo = mid;
+                else hi = mid - 1;
+            }
+            e = lo;
+            if (m > limit) {
+                for (int q = r >> 6; q <= (e - 1) >> 6; ++q) {
+                    unsigned long long b = bits[q];
+                    if (q == r >> 6) b &= ~0ull << (r & 63);
+                    if (b) {
+                        e = min(e, q * 64 + __builtin_ctzll(b));
+                        break;
+                    }
+                }
+            }
         }
-        if (rp[r + 1] - rp[r] > limit) {
-            next[r] = r + 1;
-            continue;
-        }
-        int e = min(n, r + max_rows);
-        // largest j in (r, e] with rp[j] - rp[r] <= bcap (j = r + 1 always qualifies)
-        const int cap = rp[r] + bcap;
-        int lo = r + 1, hi = e;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (rp[mid] <= cap) lo = mid;
-            else hi = mid - 1;
-        }
-        e = lo;
-        // first long row after r
-        int a = 0, b = nl;
-        while (a < b) {
-            const int mid = (a + b) >> 1;
-            if (longs[mid] <= r) a = mid + 1;
-            else b = mid;
-        }
-        if (a < nl && longs[a] < e) e = longs[a];
-        next[r] = e;
+        step[r] = (uint8_t)(e - r - 1);
     }
 }
 
-// mark[p] = (p == 0): row 0 starts the first block
-__global__ void k_mark_init(int n, int* mark) {
-    FOR_ROWS(p, (int64_t)n + 1) mark[p] = (p == 0) ? 1 : 0;
-}
-
-// One round of radix-8 doubling with jump = J: every marked start p marks
-// J(p), J^2(p), ..., J^7(p), and (if out is set) out = J^8.  A mark set by
-// another thread of the same round may be seen early; that only marks a
-// true start sooner (marks are only ever set on the orbit of row 0), so
-// after the round at least the starts within eight times the span are
-// marked, as with the rounds apart.
-__global__ void k_mark_pow8(int n, const int* jump, int* mark, int* out) {
-    FOR_ROWS(p, (int64_t)n + 1) {
-        const bool mk = mark[p] != 0;
-        int q = (int)p;
-        for (int t = 1; t < 8; ++t) {
-            q = jump[q];
-            if (mk) mark[q] = 1;
-        }
-        if (out) out[p] = jump[q];
+// f(steps, lo, hi) for every tile lo .. hi of the rows c0 .. c1, its steps in
+// LDS (step is on 16 bytes and padded to them, tiles start on 16)
+template <class F>
+__device__ __forceinline__ void for_each_tile(int c0, int c1, const uint8_t* step, F f) {
+    __shared__ uint4 lds[kChunkTile / 16];
+    for (int lo = c0; lo < c1; lo += kChunkTile) {
+        const int hi = min(c1, lo + kChunkTile);
+        const uint4* src = reinterpret_cast<const uint4*>(step + lo);
+        for (int i = threadIdx.x; i < (hi - lo + 15) / 16; i += kBlock) lds[i] = src[i];
+        __syncthreads();
+        f(reinterpret_cast<const uint8_t*>(lds), lo, hi);
+        __syncthreads();
     }
 }
 
-// out[0] = number of blocks, out[1] = threads per row, out[2] = longest row
-__global__ void k_partition_result(int n, const int* pos, const int* par, int* out) {
-    out[0] = pos[n];
-    out[1] = par[1];
-    out[2] = par[0];
+// chunk blockIdx.x walked from its row t on, for thread t: the row of the next
+// chunk that the walk enters (from its start), and the blocks that it passed
+__global__ __launch_bounds__(kBlock) void k_chunk_walks(int n, int chunk, const uint8_t* step, uint8_t* exits,
+                                                        int* counts) {
+    static_assert(kMaxStep == kBlock);
+    const int c0 = (int)blockIdx.x * chunk, c1 = min(n, c0 + chunk);
+    int r = c0 + (int)threadIdx.x, b = 0;
+    for_each_tile(c0, c1, step, [&](const uint8_t* s, int lo, int hi) {
+        while (r < hi) {
+            r += (int)s[r - lo] + 1;
+            ++b;
+        }
+    });
+    exits[blockIdx.x * kMaxStep + threadIdx.x] = (uint8_t)(r - c1);
+    counts[blockIdx.x * kMaxStep + threadIdx.x] = b;
 }
 
-__global__ void k_fill_starts(int n, const int* mark, const int* pos, int* blk) {
-    FOR_ROWS(i, n) if (mark[i]) blk[pos[i]] = (int)i;
-    if (blockIdx.x == 0 && threadIdx.x == 0) blk[pos[n]] = n;
+// where the walk from row 0 enters each chunk, and the blocks before it
+__global__ __launch_bounds__(kMaxChunks) void k_chunk_entries(int chunks, const uint8_t* exits, const int* counts,
+                                                              int* entry, int* base) {
+    __shared__ uint4 lds[kMaxChunks * kMaxStep / 16];
+    __shared__ int at[kMaxChunks];
+    __shared__ int sums[kMaxChunks / 64];
+    for (int i = threadIdx.x; i < chunks * kMaxStep / 16; i += kMaxChunks)
+        lds[i] = reinterpret_cast<const uint4*>(exits)[i];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint8_t* e = reinterpret_cast<const uint8_t*>(lds);
+        int t = 0;
+        for (int c = 0; c < chunks; ++c) {
+            at[c] = t;
+            t = e[c * kMaxStep + t];
+        }
+    }
+    __syncthreads();
+    const int c = threadIdx.x;
+    const int v = c < chunks ? counts[c * kMaxStep + at[c]] : 0;
+    const int incl = scan_add(v);
+    if ((c & 63) == 63) sums[c >> 6] = incl;
+    __syncthreads();
+    int before = incl - v;
+    for (int k = 0; k < c >> 6; ++k) before += sums[k];
+    if (c < chunks) {
+        entry[c] = at[c];
+        base[c] = before;
+    }
+}
+
+// the block starts of chunk blockIdx.x; the last one also stores the end and
+// par[0] = number of blocks
+__global__ __launch_bounds__(kBlock) void k_chunk_starts(int n, int chunk, const uint8_t* step, const int* entry,
+                                                         const int* base, int* blk, int* par) {
+    const int c0 = (int)blockIdx.x * chunk, c1 = min(n, c0 + chunk);
+    int r = c0 + (entry ? entry[blockIdx.x] : 0), b = entry ? base[blockIdx.x] : 0;
+    for_each_tile(c0, c1, step, [&](const uint8_t* s, int lo, int hi) {
+        if (threadIdx.x != 0) return;
+        while (r < hi) {
+            blk[b++] = r;
+            r += (int)s[r - lo] + 1;
+        }
+    });
+    if (c1 == n && threadIdx.x == 0) {
+        blk[b] = n;
+        par[0] = b;
+    }
 }
 
 // cbase[b] = smallest column of block b; flag = 1 if a block's columns span
@@ -468,9 +525,16 @@ __global__ __launch_bounds__(kBlock) void k_copy_lists(int nblk, const int* blkk
     }
 }
 
-// blkk[b] = rp[blk[b]] for b <= nblk
-__global__ void k_block_entries(int nblk, const int* rp, const int* blk, int* blkk) {
-    FOR_ROWS(b, (int64_t)nblk + 1) blkk[b] = rp[blk[b]];
+// the block tables at their own length: blk, blkk[b] = rp[blk[b]] (b <= nblk),
+// and cbase where it is given
+__global__ void k_block_tables(int nblk, const int* rp, const int* blk_in, const int* cbase_in, int* blk, int* blkk,
+                               int* cbase) {
+    FOR_ROWS(b, (int64_t)nblk + 1) {
+        const int r = blk_in[b];
+        blk[b] = r;
+        blkk[b] = rp[r];
+        if (cbase && b < nblk) cbase[b] = cbase_in[b];
+    }
 }
 
 }  // namespace
@@ -500,64 +564,54 @@ void stream_partition(DCsr& A, MemCounter* mc, hipStream_t s, bool pack, int cap
         return;
     }
     const int* rp = A.rowptr.get();
-    // threads per row from the longest row, decided on the device: the
-    // only read-back is the block count at the end
-    DBuf<int> par(8, mc);
-    zero_async(par.get(), 8 * sizeof(int), s);
-    hipLaunchKernelGGL(k_max_row_len, dim3(std::min(grid1(n), 256)), dim3(kBlock), 0, s, n, rp, par.get());
-    hipLaunchKernelGGL(k_group_params, dim3(1), dim3(1), 0, s, n, rp, par.get());
-    MATAMG_LAUNCH_CHECK();
-
+    // everything is decided on the device: the only read-back is {blocks,
+    // threads per row, longest row, columns too wide to pack} at the end
     const size_t n1 = (size_t)n + 1;
-    DBuf<int> flags(n1, mc), pos(n1, mc), tmp(scan_tmp_size(n1), mc), longs(n1, mc);
-    hipLaunchKernelGGL(k_long_flags, dim3(grid1(n)), dim3(kBlock), 0, s, n, rp, (const int*)par.get(), flags.get());
-    exclusive_scan(flags.get(), pos.get(), n, tmp.get(), s);
-    hipLaunchKernelGGL(k_long_list, dim3(grid1(n)), dim3(kBlock), 0, s, n, flags.get(), pos.get(), longs.get());
-    DBuf<int> ja(n1, mc), jb(n1, mc);
-    hipLaunchKernelGGL(k_block_next, dim3(grid1(n1)), dim3(kBlock), 0, s, n, rp, (const int*)par.get(), longs.get(),
-                       pos.get() + n, cap, ja.get());
-    MATAMG_LAUNCH_CHECK();
-    // pointer doubling from row 0 (flags reused as the start marks)
-    hipLaunchKernelGGL(k_mark_init, dim3(grid1(n1)), dim3(kBlock), 0, s, n, flags.get());
-    int* cur = ja.get();
-    int* nxt = jb.get();
-    for (int64_t span = 1; span <= (int64_t)n; span <<= 3) {
-        const bool more = (span << 3) <= (int64_t)n;
-        hipLaunchKernelGGL(k_mark_pow8, dim3(grid1(n1)), dim3(kBlock), 0, s, n, (const int*)cur, flags.get(),
-                           more ? nxt : (int*)nullptr);
-        if (more) std::swap(cur, nxt);
+    const int stats = std::min(grid1(n), kStatBlocks);
+    const int chunk = kChunkTile * ceil_div(ceil_div(n, kChunkTile), kMaxChunks);
+    const int chunks = ceil_div(n, chunk);
+    DBuf<int> par(4, mc), blk(n1, mc), cbase;
+    DBuf<int2> part((size_t)stats, mc);
+    DBuf<unsigned long long> bits((size_t)ceil_div(n, kBlock) * (kBlock / 64), mc);
+    DBuf<uint8_t> step(((size_t)n + 15) / 16 * 16, mc);
+    hipLaunchKernelGGL(k_row_stats, dim3(stats), dim3(kBlock), 0, s, n, rp, part.get(), bits.get());
+    hipLaunchKernelGGL(k_row_steps, dim3(grid1(n)), dim3(kBlock), 0, s, n, rp, (const int2*)part.get(), stats,
+                       (const unsigned long long*)bits.get(), cap, step.get(), par.get());
+    DBuf<uint8_t> exits;
+    DBuf<int> counts, entry;
+    if (chunks > 1) {
+        exits.alloc((size_t)chunks * kMaxStep, mc);
+        counts.alloc((size_t)chunks * kMaxStep, mc);
+        entry.alloc((size_t)chunks * 2, mc);
+        hipLaunchKernelGGL(k_chunk_walks, dim3(chunks), dim3(kBlock), 0, s, n, chunk, (const uint8_t*)step.get(),
+                           exits.get(), counts.get());
+        hipLaunchKernelGGL(k_chunk_entries, dim3(1), dim3(kMaxChunks), 0, s, chunks, (const uint8_t*)exits.get(),
+                           (const int*)counts.get(), entry.get(), entry.get() + chunks);
     }
-    MATAMG_LAUNCH_CHECK();
-    exclusive_scan(flags.get(), pos.get(), n, tmp.get(), s);
-    // block starts (at most n blocks) and, for packing, every block's
-    // column range, all before the one read-back of {blocks, group, wide}
-    DBuf<int> blk(n1 + 1, mc), cbase;
-    hipLaunchKernelGGL(k_fill_starts, dim3(grid1(n)), dim3(kBlock), 0, s, n, (const int*)flags.get(),
-                       (const int*)pos.get(), blk.get());
+    hipLaunchKernelGGL(k_chunk_starts, dim3(chunks), dim3(kBlock), 0, s, n, chunk, (const uint8_t*)step.get(),
+                       (const int*)entry.get(), (const int*)entry.get() + (chunks > 1 ? chunks : 0), blk.get(),
+                       par.get());
     if (pack && A.nnz > 0) {
         cbase.alloc(n1, mc);
         hipLaunchKernelGGL(k_block_col_range, dim3(std::min(grid1(n) * 4, 65535)), dim3(kBlock), 0, s,
-                           (const int*)pos.get() + n, rp, A.col.get(), (const int*)blk.get(), cbase.get(),
-                           par.get() + 7);
+                           (const int*)par.get(), rp, A.col.get(), (const int*)blk.get(), cbase.get(),
+                           par.get() + 3);
     }
-    hipLaunchKernelGGL(k_partition_result, dim3(1), dim3(1), 0, s, n, (const int*)pos.get(), (const int*)par.get(),
-                       par.get() + 4);
     MATAMG_LAUNCH_CHECK();
     int res[4] = {0, 0, 0, 0};
-    d2h(res, par.get() + 4, 4, s);
+    d2h(res, par.get(), 4, s);
     const int nblk = res[0];
     A.group = res[1];
     A.max_len = res[2];
     A.nblk = nblk;
     A.blk.alloc((size_t)nblk + 1, mc);
-    MATAMG_HIP(hipMemcpyAsync(A.blk.get(), blk.get(), sizeof(int) * ((size_t)nblk + 1), hipMemcpyDeviceToDevice, s));
     A.blkk.alloc((size_t)nblk + 1, mc);
-    hipLaunchKernelGGL(k_block_entries, dim3(grid1((int64_t)nblk + 1)), dim3(kBlock), 0, s, nblk, rp,
-                       (const int*)A.blk.get(), A.blkk.get());
+    const bool narrow = pack && A.nnz > 0 && res[3] == 0;
+    if (narrow) A.cbase.alloc((size_t)nblk, mc);
+    hipLaunchKernelGGL(k_block_tables, dim3(grid1((int64_t)nblk + 1)), dim3(kBlock), 0, s, nblk, rp,
+                       (const int*)blk.get(), (const int*)cbase.get(), A.blk.get(), A.blkk.get(), A.cbase.get());
     MATAMG_LAUNCH_CHECK();
-    if (pack && A.nnz > 0 && res[3] == 0) {
-        A.cbase.alloc((size_t)nblk, mc);
-        MATAMG_HIP(hipMemcpyAsync(A.cbase.get(), cbase.get(), sizeof(int) * (size_t)nblk, hipMemcpyDeviceToDevice, s));
+    if (narrow) {
         A.col16.alloc((size_t)A.nnz, mc);
         hipLaunchKernelGGL(k_pack_cols, dim3(std::min(nblk, 65535)), dim3(kBlock), 0, s, nblk, rp, A.col.get(),
                            (const int*)A.blk.get(), (const int*)A.cbase.get(), A.col16.get());
@@ -613,19 +667,18 @@ void block_uniques(DCsr& A, MemCounter* mc, hipStream_t s) {
     A.nuniq = 0;
     const int nblk = A.nblk;
     if (!A.col16 || nblk <= 0) return;
-    DBuf<int> cnt((size_t)nblk + 2, mc), tmp(scan_tmp_size((int64_t)nblk + 1), mc);
+    DBuf<int> cnt((size_t)nblk, mc), tmp(scan_tmp_size((int64_t)nblk + 1), mc);
     A.urun.alloc((size_t)nblk * kRunWords, mc);
-    zero_async(cnt.get() + nblk + 1, sizeof(int), s);
+    A.ustart.alloc((size_t)nblk + 2, mc);  // (the number of staged blocks behind the starts)
+    zero_async(A.ustart.get() + nblk + 1, sizeof(int), s);
     const int grid = std::min(nblk, 8192);
     hipLaunchKernelGGL(k_block_uniques_count, dim3(grid), dim3(kBlock), 0, s, nblk, (const int*)A.blk.get(),
                        (const int*)A.blkk.get(), (const uint16_t*)A.col16.get(), A.group, unique_cap(A.cap),
-                       cnt.get(), A.urun.get(), cnt.get() + nblk + 1);
+                       cnt.get(), A.urun.get(), A.ustart.get() + nblk + 1);
     MATAMG_LAUNCH_CHECK();
-    A.ustart.alloc((size_t)nblk + 1, mc);
     exclusive_scan(cnt.get(), A.ustart.get(), nblk, tmp.get(), s);
     int res[2] = {0, 0};  // list length, staged blocks
-    MATAMG_HIP(hipMemcpyAsync(cnt.get() + nblk, A.ustart.get() + nblk, sizeof(int), hipMemcpyDeviceToDevice, s));
-    d2h(res, cnt.get() + nblk, 2, s);
+    d2h(res, A.ustart.get() + nblk, 2, s);
     const int total = res[0];
     if (res[1] == 0) {
         // nothing staged: the streaming kernels read no per-block tables

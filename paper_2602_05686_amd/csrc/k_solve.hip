@@ -94,33 +94,77 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const int* in, int* out, 
 
 // inputs up to this length are scanned by one block of kScanOneThreads threads
 constexpr int kScanOneThreads = 1024;
-constexpr int64_t kScanOneMax = 1 << 16;
+constexpr int kScanOneTiles = 16;
+constexpr int64_t kScanOneMax = (int64_t)kScanOneThreads * 4 * kScanOneTiles;
 
 namespace {
-// the whole scan in one block: tiles of kScanOneThreads * kScanItems
-// consecutive values, each thread kScanItems of them, with a running carry
-__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int* in, int* out, int64_t n) {
-    __shared__ int sh[kScanOneThreads / 64];
-    int carry = 0;
-    for (int64_t t0 = 0; t0 < n; t0 += (int64_t)kScanOneThreads * kScanItems) {
-        const int64_t base = t0 + (int64_t)threadIdx.x * kScanItems;
-        int v[kScanItems];
-        int sum = 0;
-        for (int k = 0; k < kScanItems; ++k) {
-            const int64_t i = base + k;
-            v[k] = (i < n) ? in[i] : 0;
-            sum += v[k];
+// The whole scan in one block, in and out on 16 bytes: thread t holds values
+// 4 t .. 4 t + 3 of each tile of 4,096.  All loads go out together, then the
+// wavefronts scan their parts of every tile, and one scan of the up to 256
+// wavefront sums gives each its start: two barriers and two memory latencies
+// whatever the length (tile after tile, each a load, a scan through LDS and
+// two barriers, 27,360 values took 28 us).
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int* in, int* out, int n) {
+    constexpr int kWaves = kScanOneThreads / 64;
+    __shared__ int sums[kScanOneTiles * kWaves];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tiles = (n + 4 * kScanOneThreads - 1) / (4 * kScanOneThreads);
+    int4 v[kScanOneTiles];
+#pragma unroll
+    for (int t = 0; t < kScanOneTiles; ++t) {
+        const int i = 4 * (t * kScanOneThreads + (int)threadIdx.x);
+        v[t] = int4{0, 0, 0, 0};
+        if (i + 3 < n) {
+            v[t] = *reinterpret_cast<const int4*>(in + i);
+        } else {
+            if (i < n) v[t].x = in[i];
+            if (i + 1 < n) v[t].y = in[i + 1];
+            if (i + 2 < n) v[t].z = in[i + 2];
         }
-        int tot;
-        int ex = block_exclusive_scan(sum, sh, &tot) + carry;
-        for (int k = 0; k < kScanItems; ++k) {
-            const int64_t i = base + k;
-            if (i < n) out[i] = ex;
-            ex += v[k];
-        }
-        carry += tot;
     }
-    if (threadIdx.x == 0) out[n] = carry;
+    int incl[kScanOneTiles];
+#pragma unroll
+    for (int t = 0; t < kScanOneTiles; ++t) {
+        incl[t] = 0;
+        if (t >= tiles) continue;
+        incl[t] = scan_add(v[t].x + v[t].y + v[t].z + v[t].w);
+        if (lane == 63) sums[t * kWaves + w] = incl[t];
+    }
+    __syncthreads();
+    if (w == 0) {
+        // exclusive, in place (entries past the last tile are not read)
+        int s[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            s[k] = 4 * lane + k < tiles * kWaves ? sums[4 * lane + k] : 0;
+            sum += s[k];
+        }
+        int ex = scan_add(sum) - sum;
+        if (lane == 63) out[n] = ex + sum;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (4 * lane + k < tiles * kWaves) sums[4 * lane + k] = ex;
+            ex += s[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kScanOneTiles; ++t) {
+        if (t >= tiles) continue;
+        const int i = 4 * (t * kScanOneThreads + (int)threadIdx.x);
+        int4 o;
+        o.x = sums[t * kWaves + w] + incl[t] - (v[t].x + v[t].y + v[t].z + v[t].w);
+        o.y = o.x + v[t].x;
+        o.z = o.y + v[t].y;
+        o.w = o.z + v[t].z;
+        if (i + 3 < n) {
+            *reinterpret_cast<int4*>(out + i) = o;
+        } else {
+            if (i < n) out[i] = o.x;
+            if (i + 1 < n) out[i + 1] = o.y;
+            if (i + 2 < n) out[i + 2] = o.z;
+        }
+    }
 }
 
 __global__ void k_zero_words(uint32_t* p, int64_t n) {
@@ -155,8 +199,8 @@ void exclusive_scan(const int* in, int* out, int64_t n, int* tmp, hipStream_t s)
         zero_async(out, sizeof(int), s);
         return;
     }
-    if (n <= kScanOneMax) {
-        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, in, out, n);
+    if (n <= kScanOneMax && (((uintptr_t)in | (uintptr_t)out) & 15u) == 0) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, in, out, (int)n);
         MATAMG_LAUNCH_CHECK();
         return;
     }

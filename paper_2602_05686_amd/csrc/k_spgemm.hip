@@ -204,22 +204,6 @@ __device__ __forceinline__ void rank_columns(const int* keys, unsigned slots, in
 
 __device__ __forceinline__ int lane_int(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 
-// inclusive scans over the wavefront on the vector unit's own lane shifts
-// (within rows of 16, then row to row; lanes without a source take 0): a
-// shift through LDS costs several times as much
-template <class Op>
-__device__ __forceinline__ int wave_scan(int x, Op op) {
-    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
-    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));  // row_shr:2
-    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));  // row_shr:4
-    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));  // row_shr:8
-    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15 to rows 1 and 3
-    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31 to rows 2 and 3
-    return x;
-}
-__device__ __forceinline__ int scan_add(int x) {
-    return wave_scan(x, [](int a, int b) { return a + b; });
-}
 // the OR over the wavefront, on every lane
 __device__ __forceinline__ unsigned wave_or(unsigned x) {
     return (unsigned)lane_int(wave_scan((int)x, [](int a, int b) { return a | b; }), 63);
