@@ -13,7 +13,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmatamg.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["k_solve.hip", "k_batch.hip", "k_partition.hip", "k_rows.hip", "k_dense.hip", "k_setup.hip", "k_spgemm.hip", "hierarchy.hip", "server.hip",
+SOURCES = ["k_solve.hip", "k_tail.hip", "k_batch.hip", "k_partition.hip", "k_rows.hip", "k_dense.hip", "k_setup.hip", "k_spgemm.hip", "hierarchy.hip", "server.hip",
            "noalloc.hip", "abi.hip"]
 # setup arithmetic that decides drop masks and aggregates: one IEEE op at a time
 NO_CONTRACT = {"k_setup.hip", "k_spgemm.hip"}

@@ -47,6 +47,10 @@ struct Hierarchy {
     unsigned steps = 0;      // steps asked to report so far
     hipStream_t ws = nullptr;        // the solve's own stream
     hipEvent_t ev_in = nullptr;      // orders the solve after the caller's stream
+    // the V-cycle's last levels, tail .. nlev - 1, in one launch (0: none), in
+    // the hierarchy's precision, and the image of their operators
+    int tail = 0, tail_bytes = 0, tail_lds = 0;
+    DBuf<char> tail_img;
     double t_setup = 0.0;
     double t_update = 0.0;   // duration of the last update_values
     bool fp32 = false;
@@ -62,6 +66,9 @@ struct Hierarchy {
     double vcycle_alg_bytes() const;
     double time_smoother(int level, int reps, hipStream_t s, double* bytes_per_launch);
     void first_smooth(const double* r, hipStream_t s);
+    void build_tail(hipStream_t s);
+    template <typename T>
+    void build_tail_t(hipStream_t s);
     void ensure_solve_resources();
     void release_setup_data();
 };

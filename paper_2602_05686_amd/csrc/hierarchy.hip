@@ -701,6 +701,7 @@ std::unique_ptr<Hierarchy> build_hierarchy(int64_t n64, const int* rowptr, const
     h.cp.alloc(n0, mc);
     h.cq.alloc(n0, mc);
     h.partial2.alloc((size_t)vector_partials((int64_t)n0), mc);
+    if (wide_blocks) h.build_tail(s);  // (the server launches level by level)
     MATAMG_HIP(hipStreamSynchronize(s));
     h.t_setup = now_s() - t0;
     return hp;
@@ -778,6 +779,7 @@ void update_values(Hierarchy& h, const double* val, bool host_ptrs, hipStream_t 
         coarse_inverse_check(h, cflag.get(), s);
     }
     if (h.fp32) cast_fp32(h, s);
+    if (h.tail > 0) h.build_tail(s);
     MATAMG_HIP(hipStreamSynchronize(s));
     h.t_update = now_s() - t0;
 }
@@ -799,8 +801,9 @@ void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream
         return;
     }
     T* cur[16];
+    const int end = tail > 0 ? tail : L - 1;  // levels with launches of their own
     // restriction sweep
-    for (int l = 0; l + 1 < L; ++l) {
+    for (int l = 0; l < end; ++l) {
         Level& Lv = lev[l];
         const int n = Lv.A.n;
         T* b;
@@ -830,12 +833,16 @@ void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream
         else
             spmv<T>(Lv.R, V::A(Lv.R), V::r(Lv), V::b(Ln), s);
     }
-    // coarsest level
-    Level& Lc = lev[L - 1];
-    dense_gemv<T>(nL, Ainv.get(), V::b(Lc), V::xa(Lc), s);
-    cur[L - 1] = V::xa(Lc);
+    Level& Lc = lev[end];
+    cur[end] = V::xa(Lc);
+    if (tail > 0) {
+        tail_cycle<T>(tail_img.get(), tail_bytes, tail_lds, Lc.A.n, V::b(Lc), V::d(Lc), V::xa(Lc), V::xa(Lc), s);
+    } else {
+        // coarsest level
+        dense_gemv<T>(nL, Ainv.get(), V::b(Lc), V::xa(Lc), s);
+    }
     // prolongation sweep
-    for (int l = L - 2; l >= 0; --l) {
+    for (int l = end - 1; l >= 0; --l) {
         Level& Lv = lev[l];
         T* b;
         if constexpr (std::is_same<T, double>::value) b = (l == 0) ? const_cast<double*>(r64) : V::b(Lv);
@@ -859,6 +866,101 @@ void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream
         }
         cur[l] = x;
     }
+}
+
+// The levels below the finest that fit in LDS together (with vectors) are
+// taken by one workgroup: rows that one thread sums (the streaming kernels' one
+// thread per row, no long rows), 16-bit indices, few smoother steps.  Within
+// these limits it is always the faster: a pass over such a level takes one
+// workgroup 1 to 2 us and a launch of its own 3.5 to 5 us (FP64 V-cycles: 64^2
+// checkerboard 55 -> 44 us, 128^2 two-domain 111 -> 89 us, 512^2 182 -> 156 us).
+template <typename T>
+void Hierarchy::build_tail_t(hipStream_t s) {
+    using V = Vec<T>;
+    const int bottom = nlev - 1;
+    tail = 0;
+    if (nL > kTailDense) return;
+    auto serial = [](const DCsr& M) {
+        return M.group == 1 && M.max_len <= long_row_limit(1) && M.nnz < (1 << 16) && M.n < (1 << 16) && M.m < (1 << 16);
+    };
+    auto pad = [](int bytes) { return (bytes + 15) & ~15; };
+    auto level_bytes = [&](const Level& L) {
+        const int n = L.A.n, nnz = (int)L.A.nnz, v = (int)sizeof(T);
+        return pad(v * nnz) + pad(2 * nnz) + 2 * pad(2 * (n + 1)) + pad(2 * (L.R.n + 1)) + 5 * pad(v * n);
+    };
+    int first = bottom, bytes = pad((int)sizeof(TailHead<T>)) + 2 * pad((int)sizeof(T) * nL);
+    while (first - 1 >= 1 && bottom - (first - 1) <= kTailLevels) {
+        const Level& L = lev[first - 1];
+        if (!serial(L.A) || !serial(L.P) || !serial(L.R) || L.c1.size() > (size_t)kTailSteps) break;
+        const int need = level_bytes(L);
+        if (bytes + need > kTailLds) break;
+        bytes += need;
+        --first;
+    }
+    if (first == bottom) return;
+    // the image: operators, inverse diagonals, row pointers; the vectors follow
+    TailHead<T> a{};
+    a.levels = bottom - first;
+    TailSegments<T> segs;
+    int at = pad((int)sizeof(TailHead<T>));
+    auto values = [&](const T* p, int64_t count) {
+        segs.s[segs.count++] = TailSegment<T>{p, nullptr, (int)count, at};
+        const int here = at;
+        at += pad((int)sizeof(T) * (int)count);
+        return here;
+    };
+    auto indices = [&](const int* p, int64_t count) {
+        segs.s[segs.count++] = TailSegment<T>{nullptr, p, (int)count, at};
+        const int here = at;
+        at += pad(2 * (int)count);
+        return here;
+    };
+    for (int l = first; l < bottom; ++l) {
+        Level& L = lev[l];
+        TailLevel<T>& t = a.lv[l - first];
+        t.n = L.A.n;
+        t.steps = (int)L.c1.size();
+        t.val = values(V::A(L.A), L.A.nnz);
+        t.dinv = values(V::dinv(L), L.A.n);
+        t.col = indices(L.A.col.get(), L.A.nnz);
+        t.rp = indices(L.A.rowptr.get(), L.A.n + 1);
+        t.prp = indices(L.P.rowptr.get(), L.P.n + 1);
+        t.rrp = indices(L.R.rowptr.get(), L.R.n + 1);
+        t.pcol = L.P.col.get();
+        t.rcol = L.R.col.get();
+        t.pval = V::A(L.P);
+        t.rval = V::A(L.R);
+        for (int k = 0; k < t.steps; ++k) {
+            t.c1[k] = (T)L.c1[k];
+            t.c2[k] = (T)L.c2[k];
+        }
+    }
+    tail_bytes = at;
+    auto vector = [&](int n) {
+        const int here = at;
+        at += pad((int)sizeof(T) * n);
+        return here;
+    };
+    for (int l = 0; l < a.levels; ++l) {
+        TailLevel<T>& t = a.lv[l];
+        t.b = vector(t.n);
+        t.d = vector(t.n);
+        t.x = vector(t.n);
+        t.y = vector(t.n);
+    }
+    a.nc = nL;
+    a.bc = vector(nL);
+    a.xc = vector(nL);
+    if (tail_img.size() < (size_t)tail_bytes) tail_img.alloc((size_t)tail_bytes, &mem);
+    a.inverse = Ainv.get();
+    tail_image<T>(a, segs, tail_img.get(), s);
+    tail_lds = at;
+    tail = first;
+}
+
+void Hierarchy::build_tail(hipStream_t s) {
+    if (fp32) build_tail_t<float>(s);
+    else build_tail_t<double>(s);
 }
 
 // the finest level's first smoother step from r, as the V-cycle takes it
@@ -892,6 +994,12 @@ double Hierarchy::vcycle_alg_bytes() const {
         const double n = L.A.n, nc = L.nc;
         const double steps = (double)L.c1.size();
         auto matrix = [&](const DCsr& M) { return M.stream_bytes(s); };
+        if (tail > 0 && l >= tail) {
+            // in one workgroup's LDS: every matrix and dinv once, and the
+            // first level's b, d and x in and x out
+            bytes += matrix(L.A) + matrix(L.R) + matrix(L.P) + s * n * (l == tail ? 5.0 : 1.0);
+            continue;
+        }
         // smoother SpMVs: (steps-1) pre + steps post; one residual SpMV
         const double n_spmv = (steps - 1.0) + steps + 1.0;
         bytes += n_spmv * matrix(L.A);

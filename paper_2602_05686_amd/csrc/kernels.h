@@ -132,4 +132,52 @@ void dense_gemv(int n, const double* M, const T* in, T* out, hipStream_t s);
 // not positive definite, and A then holds no inverse.  work: n*n doubles.
 void dense_spd_inverse(int n, double* A, double* work, int* flag, hipStream_t s);
 
+// ------------------------------------------------- the V-cycle's small levels ---
+constexpr int kTailLevels = 4;       // smoothed levels
+constexpr int kTailSteps = 4;        // smoother steps
+constexpr int kTailDense = 256;      // coarsest unknowns
+constexpr int kTailLds = 156 << 10;  // bytes
+
+constexpr int kTailThreads = 1024;
+// One level in LDS: byte offsets of its arrays, the operator's, the inverse
+// diagonal and the row pointers in the image.  The transfers' entries are in
+// memory.
+template <typename T>
+struct TailLevel {
+    int n, steps;
+    int val, col, dinv, rp, prp, rrp;  // operator; row pointers of P and R
+    int b, d, x, y;
+    const int *pcol, *rcol;
+    const T *pval, *rval;
+    T c1[kTailSteps], c2[kTailSteps];
+};
+// the head of the image
+template <typename T>
+struct TailHead {
+    int levels;
+    int nc, bc, xc;  // coarsest unknowns, right-hand side and solution
+    const double* inverse;
+    TailLevel<T> lv[kTailLevels];
+};
+// an array of the image: values, or indices to be stored in 16 bits
+template <typename T>
+struct TailSegment {
+    const T* val;
+    const int* idx;
+    int count, at;
+};
+template <typename T>
+struct TailSegments {
+    int count = 0;
+    TailSegment<T> s[6 * kTailLevels];
+};
+template <typename T>
+void tail_image(const TailHead<T>& head, const TailSegments<T>& segs, char* image, hipStream_t s);
+// the V-cycle from the first of the levels (n rows, its right-hand side b, its
+// first smoother step in d and x) down and back, its result to out; that
+// level's b, d and x lie behind the image in LDS, in this order
+template <typename T>
+void tail_cycle(const char* image, int image_bytes, int lds_bytes, int n, const T* b, const T* d, const T* x, T* out,
+                hipStream_t s);
+
 }  // namespace matamg
