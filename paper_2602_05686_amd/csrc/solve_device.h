@@ -86,9 +86,14 @@ __device__ __forceinline__ RowOperands<T> row_operands(const SArgs<T>& a, int r)
     return o;
 }
 
+// the factors of a row's term of the fused dot product
+struct DotTerm {
+    double a, b;
+};
+
 template <typename T, int MODE, bool HAS_DOT>
-__device__ __forceinline__ double epilogue(const SArgs<T>& a, int r, T s, const RowOperands<T>& o) {
-    double dp = 0.0;
+__device__ __forceinline__ DotTerm epilogue(const SArgs<T>& a, int r, T s, const RowOperands<T>& o) {
+    DotTerm dp{0.0, 0.0};
     if constexpr (MODE == M_PLAIN) {
         a.y[r] = s;
     } else if constexpr (MODE == M_RESID) {
@@ -102,18 +107,18 @@ __device__ __forceinline__ double epilogue(const SArgs<T>& a, int r, T s, const 
         T xn = o.xin + dn;
         if (a.y64) a.y64[r] = (double)xn;
         else a.y[r] = xn;
-        if constexpr (HAS_DOT) dp = (double)xn * a.dotvec[r];
+        if constexpr (HAS_DOT) dp = DotTerm{(double)xn, a.dotvec[r]};
     } else if constexpr (MODE == M_DOTPQ) {
         a.y[r] = s;
-        dp = (double)o.xin * (double)s;
+        dp = DotTerm{(double)o.xin, (double)s};
     } else if constexpr (MODE == M_RESNORM) {
         T v = o.b - s;
         a.y[r] = v;
-        dp = (double)v * (double)v;
+        dp = DotTerm{(double)v, (double)v};
     } else if constexpr (MODE == M_SCALENORM) {
         T v = o.dinv * s;
         a.y[r] = v;
-        dp = (double)v * (double)v;
+        dp = DotTerm{(double)v, (double)v};
     } else if constexpr (MODE == M_RESTRICT) {
         // the coarse right-hand side, and the first smoother step from a
         // zero iterate (the same operations as smooth_first_body)
@@ -463,7 +468,10 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
                 if (wide && rank >= base && rank < base + 8) s = got;
                 for (int j = 0; j < 8; ++j) wm &= wm - 1ull;
             }
-            if (owner) dp = epilogue<T, MODE, HAS_DOT>(a, r, s, ops);
+            if (owner) {
+                const DotTerm t = epilogue<T, MODE, HAS_DOT>(a, r, s, ops);
+                dp = t.a * t.b;
+            }
         } else {
             // G threads per row: strided partial sums, then a fixed shuffle
             // tree (on every thread the same bits), row after row; the row's
@@ -477,14 +485,15 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
                 for (int off = G / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, G);
                 if (gl == q) s = t;
             }
-            double e = 0.0;
+            DotTerm e{0.0, 0.0};
             if (owner) e = epilogue<T, MODE, HAS_DOT>(a, r, s, ops);
             if constexpr (HAS_DOT) {
-                // the group's terms in row order, on its first thread
+                // the group's terms in row order, each product and addition
+                // rounded once, on its first thread
 #pragma unroll
                 for (int q = 0; q < RQ; ++q) {
-                    const double t = __shfl(e, q, G);
-                    if (gl == 0) dp += t;
+                    const double ta = __shfl(e.a, q, G), tb = __shfl(e.b, q, G);
+                    if (gl == 0 && r + q * (kBlock / G) < r1) dp = __builtin_fma(ta, tb, dp);
                 }
             }
         }
@@ -523,7 +532,8 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         if (threadIdx.x == 0) {
             T t = S.shr[0];
             for (int i = 1; i < kBlock / 64; ++i) t += S.shr[i];
-            dp = epilogue<T, MODE, HAS_DOT>(a, r0, t, row_operands<T, MODE>(a, r0));
+            const DotTerm p = epilogue<T, MODE, HAS_DOT>(a, r0, t, row_operands<T, MODE>(a, r0));
+            dp = p.a * p.b;
         }
     }
     if constexpr (HAS_DOT) {
@@ -674,8 +684,8 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
             const T* x = a.x + r;
             s = row_sum<T>(lv, k0, len, [&](int k) { return operand<MODE>(x[lo[k]], scale); });
         }
-        const double dp = epilogue<T, MODE, HAS_DOT>(a, r, s, o);
-        if constexpr (HAS_DOT) ld[r - r0] = dp;
+        const DotTerm dp = epilogue<T, MODE, HAS_DOT>(a, r, s, o);
+        if constexpr (HAS_DOT) ld[r - r0] = dp.a * dp.b;
     }
     if constexpr (HAS_DOT) {
         __syncthreads();
