@@ -909,7 +909,7 @@ def main():
         "op_complexity": st["op_complexity"],
         "vcycle": {"ms": t_vc_ms, "alg_bytes": st["vcycle_alg_bytes"], "alg_GBps": vc_gbs,
                    "frac_of_peak": vc_gbs / HBM_PEAK_GBS},
-        "roofline": {"bound": "hbm", "kernel": "k_stream<double, SMOOTH> on the finest level",
+        "roofline": {"bound": "hbm", "kernel": "fused FP64 Chebyshev SpMV on the finest level (k_rows<double, SMOOTH>)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic, "avg_launch_us": avg_ms * 1e3, "launches": args.vcycles,
                      "alg_bytes_per_launch": kt["bytes_per_launch"],
