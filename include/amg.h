@@ -246,9 +246,10 @@ amg_status amg_get_level_aux(const amg_hierarchy* h, int32_t level, int32_t whic
  * back-to-back launches of the level's fused smoother step (the Chebyshev
  * SpMV with its vector epilogue) on the hierarchy's own work vectors between
  * two HIP events recorded on `hip_stream`, and returns the average launch
- * duration in ms and the algorithmic bytes one launch moves: matrix values,
- * column indices and row pointers once, the gathered iterate once, b, D^{-1}
- * and the direction read, the direction and the new iterate written.
+ * duration in ms and the algorithmic bytes one launch moves: the matrix as the
+ * launch reads it once (values, column indices and row pointers, or the row
+ * dictionaries of an operator whose rows repeat), the gathered iterate once, b,
+ * D^{-1} and the direction read, the direction and the new iterate written.
  * Overwrites the level's work vectors.  Errors: INVALID_ARG (no smoother on
  * that level, reps < 1). */
 amg_status amg_time_smoother(amg_hierarchy* h, int32_t level, int32_t reps, void* hip_stream, double* avg_ms,
