@@ -79,7 +79,7 @@ template <typename T, int MODE, bool HAS_DOT>
 void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg, int total, const RowsSize& rs,
                     hipStream_t s) {
     if (group == 0) {
-        const RowsSize z = rows_size<T>(rs.max_e, rs.max_n, rs.max_x, HAS_DOT ? kDictGroupRows : 0);
+        const RowsSize z = rows_size<T>(rs.max_e, rs.max_n, rs.max_x, HAS_DOT ? kDictGroupRows : 0, kRowsStageRows);
         hipLaunchKernelGGL((k_rows_batch<T, MODE, HAS_DOT>), dim3(xcd_grid(total)), dim3(kBlock), rows_lds<T>(z).bytes, s,
                            args, starts, nseg, total, z);
     } else if (group == 1)

@@ -319,7 +319,7 @@ void launch_stream(const DCsr& A, const SArgs<T>& a, hipStream_t s) {
         hipLaunchKernelGGL(kernel, dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s, a.blk, a.blkk, A.nblk, a);
     };
     if (a.dk > 0) {
-        const RowsSize z = rows_size<T>(A.dmax_e, A.dmax_n, A.dmax_x, HAS_DOT ? a.dk * kMaxRowsPerBlock : 0);
+        const RowsSize z = rows_size<T>(A.dmax_e, A.dmax_n, A.dmax_x, HAS_DOT ? a.dk * kMaxRowsPerBlock : 0, A.n);
         hipLaunchKernelGGL((k_rows<T, MODE, HAS_DOT>), dim3(xcd_grid(A.dgroups())), dim3(kBlock), rows_lds<T>(z).bytes,
                            s, a.blk, a.drun, A.dgroups(), a, z);
     } else if (A.group == 1 && A.cap == kStreamCapWide) {

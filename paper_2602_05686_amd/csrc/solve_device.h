@@ -707,12 +707,19 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
 // staged for FP64 operands where six workgroups' LDS fits a CU: FP32 gathers
 // (half the bytes) and groups with large dictionaries lose more by the lower
 // occupancy and the barrier (FP32 fine smoother of the 128^3 stack 25 us
-// staged, 20 us gathering; FP64 of the 96^3 cube 28 us and 25 us).
+// staged, 20 us gathering; FP64 of the 96^3 cube 28 us and 25 us).  A launch of
+// fewer rows gathers too: its workgroups are all resident at once and staging is
+// one more step of their chain (FP64 smoothers gathering and staged: 15 thousand
+// rows of 27 entries 4.0 and 4.7 us, 27 thousand 4.2 and 5.2, 91 thousand 5.4
+// and 5.8; 118 thousand 5.9 and 5.7, 531 thousand 13.0 and 11.1).
 constexpr int kRowsStageLds = 160 * 1024 / 6;
+constexpr int kRowsStageRows = 100000;
 template <typename T>
-inline RowsSize rows_size(int max_e, int max_n, int max_x, int dots) {
+inline RowsSize rows_size(int max_e, int max_n, int max_x, int dots, int rows) {
     RowsSize z{max_e, max_n, max_x, dots};
-    if (sizeof(T) == 4 || rows_lds<T>(RowsSize{max_e, max_n, max_x, 0}).bytes > kRowsStageLds) z.max_x = 0;
+    if (sizeof(T) == 4 || rows < kRowsStageRows ||
+        rows_lds<T>(RowsSize{max_e, max_n, max_x, 0}).bytes > kRowsStageLds)
+        z.max_x = 0;
     return z;
 }
 
