@@ -8,6 +8,7 @@
 
 #include <exception>
 
+#include "cg_host.h"
 #include "hierarchy.h"
 #include "setup_kernels.h"
 
@@ -1086,10 +1087,6 @@ size_t pcg_partials(const Hierarchy& h) {
 
 // The PCG iteration on an explicit workspace (see PcgWork): the convergence
 // test reads the device scalars after every step through w.hscal.
-// the part of the foreseen residual that has to be above the tolerance for
-// the next V-cycle to be launched ahead
-constexpr double kAheadMargin = 0.5;
-
 amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, int max_iter, int* iters_out,
                    double* rel_out) {
     const DCsr& A = h.lev[0].A;
@@ -1138,7 +1135,7 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
         bool ahead = false;
         auto step = [&](int it) {
             if (!ahead) cg_precondition(h, w, cur, fused && it > 1);
-            ahead = w.partial2 && it < max_iter && last * rate * kAheadMargin > tol;
+            ahead = w.partial2 && look_ahead(h.nlev, it, max_iter, last, rate, tol);
             cg_advance(h, w, cur, old, it == 1);
             if (ahead) cg_precondition(h, w, cur, fused);
             if (w.partial2) ++h.steps;
