@@ -1058,22 +1058,21 @@ void cg_advance(Hierarchy& h, const PcgWork& w, int nxt, int old, bool first) {
                       h.counter.get() + 1, h.hscal, h.hstep(), s);
 }
 
-// Waits for the last step asked to report.  The scalars arrive in pinned
-// memory a few microseconds before a copy and a stream synchronisation would
-// bring them, which small systems' steps would wait out each time.
-void wait_report(Hierarchy& h, hipStream_t s) {
-    for (unsigned spin = 1;; ++spin) {
-        if ((int)(__atomic_load_n(h.hstep(), __ATOMIC_ACQUIRE) - h.steps) >= 0) return;
-        if (spin % 4096 == 0) {
+// Waits for the last step asked to report (ahead: the next V-cycle is behind
+// it).  The scalars arrive in pinned memory a few microseconds before a copy and
+// a stream synchronisation would bring them, which small systems' steps would
+// wait out each time.
+void wait_report(Hierarchy& h, bool ahead, hipStream_t s) {
+    const bool reported = wait_until(
+        ahead, [&] { return (int)(__atomic_load_n(h.hstep(), __ATOMIC_ACQUIRE) - h.steps) >= 0; },
+        [&] {
             const hipError_t e = hipStreamQuery(s);
-            if (e == hipErrorNotReady) continue;
+            if (e == hipErrorNotReady) return false;
             if (e != hipSuccess) (void)hipGetLastError();
             MATAMG_HIP(e);
-            // the stream is idle: the step has reported, or never will
-            if ((int)(__atomic_load_n(h.hstep(), __ATOMIC_ACQUIRE) - h.steps) >= 0) return;
-            fail(AMG_ERR_HIP, "a CG step ended without reporting its scalars");
-        }
-    }
+            return true;
+        });
+    if (!reported) fail(AMG_ERR_HIP, "a CG step ended without reporting its scalars");
 }
 
 }  // namespace
@@ -1142,7 +1141,7 @@ amg_status pcg_run(Hierarchy& h, const PcgWork& w, const double* b, double tol, 
         };
         step(1);
         for (int it = 1;; ++it) {
-            if (w.partial2) wait_report(h, ws);
+            if (w.partial2) wait_report(h, ahead, ws);
             else read_scal();
             iters = it;
             const double pq = w.hscal[S_PQ], rzv = w.hscal[cur];
