@@ -242,6 +242,19 @@ amg_status amg_get_level_csr(const amg_hierarchy* h, int32_t level, int32_t whic
                              int32_t* col, double* val);
 amg_status amg_get_level_aux(const amg_hierarchy* h, int32_t level, int32_t which, double* out);
 
+/* How the V-cycle's kernels read a matrix of a level (which as for
+ * amg_get_level_csr), for tests and benchmarks.  form: int32 [8]
+ *  0  threads per row (1 or 8)
+ *  1  most stored entries of a row block, 2 its number of row blocks
+ *  3  columns: 0 32 bits, 1 16 bits from one base per row block, 2 16 bits by
+ *     windows of columns
+ *  4  entries in row blocks that have windows
+ *  5  groups of rows that have a dictionary (0: values and columns are streamed)
+ *  6  1 if FP64 launches stage a group's part of the gathered vector
+ *  7  1 if the level is among the last ones, which one workgroup takes
+ * Errors: INVALID_ARG. */
+amg_status amg_get_level_form(const amg_hierarchy* h, int32_t level, int32_t which, int32_t* form);
+
 /* Roofline timing of the dominant kernel (benchmarks): runs `reps`
  * back-to-back launches of the level's fused smoother step (the Chebyshev
  * SpMV with its vector epilogue) on the hierarchy's own work vectors between

@@ -24,12 +24,14 @@ PTR_HOST, PTR_DEVICE = 0, 1
 SOC = {"material": 0, "distance": 1, "sa": 2}
 SMOOTHER = {"chebyshev": 0, "jacobi": 1, "jacobi_scaled": 2}
 PRECISION = {"fp64": 0, "fp32": 1}
+MATRIX = {"A": 0, "P": 1, "R": 2}
 DROP = {"pointwise": 0, "cut": 1}
 
 EXPORTED = [
     "amg_options_default", "amg_setup", "amg_pcg_solve", "amg_pcg_solve_noalloc", "amg_update_values", "amg_vcycle", "amg_level_spmv",
     "amg_hierarchy_info",
-    "amg_get_aggregates", "amg_get_soc_mask", "amg_get_level_csr", "amg_get_level_aux", "amg_time_smoother",
+    "amg_get_aggregates", "amg_get_soc_mask", "amg_get_level_csr", "amg_get_level_aux", "amg_get_level_form",
+    "amg_time_smoother",
     "amg_free", "amg_trim_cache", "amg_status_string", "amg_last_error",
     "amg_server_create", "amg_server_submit", "amg_server_poll", "amg_server_result", "amg_server_info",
     "amg_server_set_batch_wait", "amg_server_destroy",
@@ -132,6 +134,7 @@ def load():
     L.amg_get_soc_mask.argtypes = [P, i32, P]
     L.amg_get_level_csr.argtypes = [P, i32, i32, P, P, P]
     L.amg_get_level_aux.argtypes = [P, i32, i32, P]
+    L.amg_get_level_form.argtypes = [P, i32, i32, P]
     L.amg_time_smoother.argtypes = [P, i32, i32, P, ctypes.POINTER(f64), ctypes.POINTER(f64)]
     L.amg_free.argtypes = [P]
     L.amg_free.restype = None
@@ -322,7 +325,7 @@ class Hierarchy:
 
     def level_csr(self, level, which="A"):
         st = self.stats()
-        w = {"A": 0, "P": 1, "R": 2}[which]
+        w = MATRIX[which]
         if w == 0:
             rows, nnz = st["n"][level], st["nnz"][level]
         elif w == 1:
@@ -334,6 +337,16 @@ class Hierarchy:
         va = np.zeros(nnz, dtype=np.float64)
         check(load().amg_get_level_csr(self._h, level, w, _hp(rp), _hp(ci), _hp(va)), "amg_get_level_csr")
         return rp, ci, va
+
+    def level_form(self, level, which="A"):
+        """How the V-cycle's kernels read the matrix (amg_get_level_form)."""
+        f = np.zeros(8, dtype=np.int32)
+        check(load().amg_get_level_form(self._h, level, MATRIX[which], _hp(f)), "amg_get_level_form")
+        keys = ("threads_per_row", "block_entries", "blocks", "columns", "windowed_entries", "dictionaries", "staged",
+                "one_workgroup")
+        out = dict(zip(keys, f.tolist()))
+        out["columns"] = ("32-bit", "16-bit", "windows")[out["columns"]]
+        return out
 
     def level_aux(self, level, which):
         st = self.stats()

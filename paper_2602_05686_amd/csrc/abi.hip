@@ -393,15 +393,19 @@ amg_status amg_get_soc_mask(const amg_hierarchy* hh, int32_t level, uint8_t* mas
     });
 }
 
+static const DCsr& level_matrix(const Hierarchy& h, int level, int which) {
+    if (level < 0 || level >= h.nlev) fail(AMG_ERR_INVALID_ARG, "level out of range");
+    if (which < 0 || which > 2 || (which > 0 && level + 1 >= h.nlev))
+        fail(AMG_ERR_INVALID_ARG, "no such matrix on this level");
+    const Level& L = h.lev[level];
+    return which == 0 ? L.A : (which == 1 ? L.P : L.R);
+}
+
 amg_status amg_get_level_csr(const amg_hierarchy* hh, int32_t level, int32_t which, int32_t* rowptr,
                              int32_t* col, double* val) {
     return guarded([&]() -> amg_status {
         const Hierarchy& h = H(hh);
-        if (level < 0 || level >= h.nlev) fail(AMG_ERR_INVALID_ARG, "level out of range");
-        if (which < 0 || which > 2 || (which > 0 && level + 1 >= h.nlev))
-            fail(AMG_ERR_INVALID_ARG, "no such matrix on this level");
-        const Level& L = h.lev[level];
-        const DCsr& M = which == 0 ? L.A : (which == 1 ? L.P : L.R);
+        const DCsr& M = level_matrix(h, level, which);
         if (rowptr) MATAMG_HIP(hipMemcpy(rowptr, M.rowptr.get(), sizeof(int) * ((size_t)M.n + 1), hipMemcpyDeviceToHost));
         if (col) MATAMG_HIP(hipMemcpy(col, M.col.get(), sizeof(int) * (size_t)M.nnz, hipMemcpyDeviceToHost));
         if (val) MATAMG_HIP(hipMemcpy(val, M.val.get(), sizeof(double) * (size_t)M.nnz, hipMemcpyDeviceToHost));
@@ -430,6 +434,23 @@ amg_status amg_get_level_aux(const amg_hierarchy* hh, int32_t level, int32_t whi
         } else {
             fail(AMG_ERR_INVALID_ARG, "unknown aux array");
         }
+        return AMG_OK;
+    });
+}
+
+amg_status amg_get_level_form(const amg_hierarchy* hh, int32_t level, int32_t which, int32_t* form) {
+    return guarded([&]() -> amg_status {
+        const Hierarchy& h = H(hh);
+        const DCsr& M = level_matrix(h, level, which);
+        if (!form) fail(AMG_ERR_INVALID_ARG, "form is null");
+        form[0] = M.group;
+        form[1] = M.cap;
+        form[2] = M.nblk;
+        form[3] = M.uwin ? 2 : M.col16 ? 1 : 0;
+        form[4] = M.uwin ? (int32_t)M.npacked : 0;
+        form[5] = M.dgroups();
+        form[6] = rows_staged(M) ? 1 : 0;
+        form[7] = h.tail > 0 && level >= h.tail ? 1 : 0;
         return AMG_OK;
     });
 }

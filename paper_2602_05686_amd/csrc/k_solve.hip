@@ -353,6 +353,10 @@ SArgs<T> base_args(const DCsr& A, const T* val, const T* x) {
 }
 }  // namespace
 
+bool rows_staged(const DCsr& A) {
+    return A.dk > 0 && rows_size<double>(A.dmax_e, A.dmax_n, A.dmax_x, 0, A.n).max_x > 0;
+}
+
 template <typename T>
 void spmv(const DCsr& A, const T* val, const T* x, T* y, hipStream_t s) {
     auto a = base_args<T>(A, val, x);

@@ -40,6 +40,8 @@ void block_windows(DCsr& A, MemCounter* mc, hipStream_t s);
 // the row dictionaries of A (see DCsr::drow_of) where its rows repeat; none
 // otherwise.  Synchronises s.
 void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s);
+// whether FP64 launches stage the windows that A's dictionaries gather from
+bool rows_staged(const DCsr& A);
 
 // dot partials of a streaming launch: one per row block
 constexpr int kStreamPartials = 1;  // dot partials per streaming block
