@@ -871,10 +871,14 @@ void Hierarchy::vcycle_t(const double* r64, double* z64, DotTarget rz, hipStream
 
 // The levels below the finest that fit in LDS together (with vectors) are
 // taken by one workgroup: rows that one thread sums (the streaming kernels' one
-// thread per row, no long rows), 16-bit indices, few smoother steps.  Within
-// these limits it is always the faster: a pass over such a level takes one
-// workgroup 1 to 2 us and a launch of its own 3.5 to 5 us (FP64 V-cycles: 64^2
-// checkerboard 55 -> 44 us, 128^2 two-domain 111 -> 89 us, 512^2 182 -> 156 us).
+// thread per row), 16-bit indices, few smoother steps, and no row longer than
+// kTailRow.  A pass over such a level takes one workgroup 1 to 2 us and a launch
+// of its own 3.5 to 5 us, but here its longest row is one thread's chain, where the
+// launches have eight.  Gain of a level's place here over its seven launches, by
+// its longest row (2D and 3D problems, 12 to 728 rows, both precisions): up to 30
+// entries 7 to 13 us, 40 to 90 1 to 17 us, 97 0 to 2 us, 129 -1 to 3 us, 144 -2 to
+// -5 us, 158 to 229 -6 to -15 us.  FP64 V-cycles: 64^2 checkerboard 55 -> 44 us,
+// 128^2 two-domain 111 -> 89 us, 512^2 182 -> 156 us.
 template <typename T>
 void Hierarchy::build_tail_t(hipStream_t s) {
     using V = Vec<T>;
@@ -882,7 +886,7 @@ void Hierarchy::build_tail_t(hipStream_t s) {
     tail = 0;
     if (nL > kTailDense) return;
     auto serial = [](const DCsr& M) {
-        return M.group == 1 && M.max_len <= long_row_limit(1) && M.nnz < (1 << 16) && M.n < (1 << 16) && M.m < (1 << 16);
+        return M.group == 1 && M.max_len <= kTailRow && M.nnz < (1 << 16) && M.n < (1 << 16) && M.m < (1 << 16);
     };
     auto pad = [](int bytes) { return (bytes + 15) & ~15; };
     auto level_bytes = [&](const Level& L) {

@@ -138,6 +138,7 @@ void dense_spd_inverse(int n, double* A, double* work, int* flag, hipStream_t s)
 constexpr int kTailLevels = 4;       // smoothed levels
 constexpr int kTailSteps = 4;        // smoother steps
 constexpr int kTailDense = 256;      // coarsest unknowns
+constexpr int kTailRow = 96;         // entries of a row
 constexpr int kTailLds = 156 << 10;  // bytes
 
 constexpr int kTailThreads = 1024;

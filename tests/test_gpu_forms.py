@@ -110,6 +110,32 @@ def test_last_levels_in_one_workgroup(shape, contrast, max_coarse, first, smooth
     h.close()
 
 
+# layered stacks: levels with rows of 110 to 170 entries among narrower ones
+@pytest.mark.parametrize("n,max_coarse", [(16, 20), (24, 10), (24, 60), (30, 20)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_levels_with_long_rows_keep_their_launches(n, max_coarse, precision):
+    import paper_2602_05686_amd as amg
+    from workloads import layered_stack_3d
+
+    p = layered_stack_3d(n=n, repeats=4)
+    kw = dict(max_coarse=max_coarse, max_levels=16, precision=precision)
+    h = amg.Hierarchy.from_problem(p, **kw)
+    levels = h.stats()["levels"]
+    longest = [max(int(np.diff(h.level_csr(l, w)[0]).max()) for w in "APR") for l in range(levels - 1)]
+    taken = [bool(h.level_form(l)["one_workgroup"]) for l in range(levels)]
+    start = levels - 1
+    while longest[start - 1] <= 96:
+        start -= 1
+    # (the narrow levels below the first long row are few and small enough)
+    assert any(100 < m <= 256 for m in longest[1:])
+    assert taken == [l >= start and start < levels - 1 for l in range(levels)]
+    with amg.Server(budget_bytes=2 << 30, dim=p.dim, **kw) as srv:
+        ref = srv.result(tail._done(srv, srv.submit(p, tol=1e-8, max_iter=60)))[0]
+    x, _ = h.solve(p.b, tol=1e-8, max_iter=60, raise_on_error=False)
+    assert np.array_equal(x, ref)
+    h.close()
+
+
 def _csr(rcv, shape):
     import scipy.sparse as sp
 
