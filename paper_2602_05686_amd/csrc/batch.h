@@ -14,11 +14,15 @@ namespace matamg {
 // streaming SpMV of mode `mode` (StreamMode) with `group` threads per row
 // (1 or 8; segment j has the matrix's row-block count), or from the row
 // dictionaries (group 0; segment j has the matrix's group count, rs the
-// largest sizes among the records).
+// largest sizes among the records and the rows and entries of all).
 // Precision: float or double records.
+struct RowsBatch {
+    RowsSize size;
+    int64_t rows = 0, entries = 0;
+};
 template <typename T>
 void stream_batch(int mode, bool has_dot, int group, const SArgs<T>* args, const int* starts, int nseg, int total,
-                  const RowsSize& rs, hipStream_t s);
+                  const RowsBatch& rs, hipStream_t s);
 // segment j has vec_grid(n_j) blocks
 template <typename T>
 void smooth_first_batch(const SmoothFirstArgs<T>* args, const int* starts, int nseg, int total, hipStream_t s);

@@ -76,10 +76,11 @@ __global__ __launch_bounds__(kBlock) void k_gemv_batch(const GemvArgs<T>* args, 
 }
 
 template <typename T, int MODE, bool HAS_DOT>
-void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg, int total, const RowsSize& rs,
+void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg, int total, const RowsBatch& rs,
                     hipStream_t s) {
     if (group == 0) {
-        const RowsSize z = rows_size<T>(rs.max_e, rs.max_n, rs.max_x, HAS_DOT ? kDictGroupRows : 0, kRowsStageRows);
+        const RowsSize z = rows_size<T>(rs.size.max_e, rs.size.max_n, rs.size.max_x, HAS_DOT ? kDictGroupRows : 0, rs.rows,
+                                        rs.entries);
         hipLaunchKernelGGL((k_rows_batch<T, MODE, HAS_DOT>), dim3(xcd_grid(total)), dim3(kBlock), rows_lds<T>(z).bytes, s,
                            args, starts, nseg, total, z);
     } else if (group == 1)
@@ -94,7 +95,7 @@ void stream_batch_t(int group, const SArgs<T>* args, const int* starts, int nseg
 
 template <typename T>
 void stream_batch(int mode, bool has_dot, int group, const SArgs<T>* args, const int* starts, int nseg, int total,
-                  const RowsSize& rs, hipStream_t s) {
+                  const RowsBatch& rs, hipStream_t s) {
     if (nseg <= 0 || total <= 0) return;
     if (group != 0 && group != 1 && group != 8) fail(AMG_ERR_INVALID_ARG, "batched SpMV: group must be 0, 1 or 8");
     switch (mode) {
@@ -109,8 +110,8 @@ void stream_batch(int mode, bool has_dot, int group, const SArgs<T>* args, const
         default: fail(AMG_ERR_INVALID_ARG, "batched SpMV: unsupported mode");
     }
 }
-template void stream_batch<float>(int, bool, int, const SArgs<float>*, const int*, int, int, const RowsSize&, hipStream_t);
-template void stream_batch<double>(int, bool, int, const SArgs<double>*, const int*, int, int, const RowsSize&, hipStream_t);
+template void stream_batch<float>(int, bool, int, const SArgs<float>*, const int*, int, int, const RowsBatch&, hipStream_t);
+template void stream_batch<double>(int, bool, int, const SArgs<double>*, const int*, int, int, const RowsBatch&, hipStream_t);
 
 template <typename T>
 void smooth_first_batch(const SmoothFirstArgs<T>* args, const int* starts, int nseg, int total, hipStream_t s) {

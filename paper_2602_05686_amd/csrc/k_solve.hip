@@ -319,7 +319,8 @@ void launch_stream(const DCsr& A, const SArgs<T>& a, hipStream_t s) {
         hipLaunchKernelGGL(kernel, dim3(xcd_grid(A.nblk)), dim3(kBlock), 0, s, a.blk, a.blkk, A.nblk, a);
     };
     if (a.dk > 0) {
-        const RowsSize z = rows_size<T>(A.dmax_e, A.dmax_n, A.dmax_x, HAS_DOT ? a.dk * kMaxRowsPerBlock : 0, A.n);
+        const RowsSize z = rows_size<T>(A.dmax_e, A.dmax_n, A.dmax_x, HAS_DOT ? a.dk * kMaxRowsPerBlock : 0, A.n,
+                                      A.nnz);
         hipLaunchKernelGGL((k_rows<T, MODE, HAS_DOT>), dim3(xcd_grid(A.dgroups())), dim3(kBlock), rows_lds<T>(z).bytes,
                            s, a.blk, a.drun, A.dgroups(), a, z);
     } else if (A.group == 1 && A.cap == kStreamCapWide) {
@@ -354,7 +355,7 @@ SArgs<T> base_args(const DCsr& A, const T* val, const T* x) {
 }  // namespace
 
 bool rows_staged(const DCsr& A) {
-    return A.dk > 0 && rows_size<double>(A.dmax_e, A.dmax_n, A.dmax_x, 0, A.n).max_x > 0;
+    return A.dk > 0 && rows_size<double>(A.dmax_e, A.dmax_n, A.dmax_x, 0, A.n, A.nnz).max_x > 0;
 }
 
 template <typename T>

@@ -94,7 +94,7 @@ struct Stage {
     std::vector<SArgs<T>> s[3];  // by threads per row: 1, 8; from row dictionaries
     std::vector<SArgs<double>> d[3];
     std::vector<int> sn[3];      // row blocks (dictionary groups) per record
-    RowsSize rs;                 // largest dictionary
+    RowsBatch rs;                // largest dictionary, rows and entries of all
     std::vector<SmoothFirstArgs<T>> sf;
     std::vector<GemvArgs<T>> gv;
     std::vector<CgDirArgs> cd;
@@ -132,9 +132,11 @@ int stream_slot(S& s, const DCsr& M, const A& a) {
         return g;
     }
     s.sn[2].push_back(M.dgroups());
-    s.rs.max_e = std::max(s.rs.max_e, M.dmax_e);
-    s.rs.max_n = std::max(s.rs.max_n, M.dmax_n);
-    s.rs.max_x = std::max(s.rs.max_x, M.dmax_x);
+    s.rs.size.max_e = std::max(s.rs.size.max_e, M.dmax_e);
+    s.rs.size.max_n = std::max(s.rs.size.max_n, M.dmax_n);
+    s.rs.size.max_x = std::max(s.rs.size.max_x, M.dmax_x);
+    s.rs.rows += M.n;
+    s.rs.entries += M.nnz;
     return 2;
 }
 constexpr int kSlotGroup[3] = {1, 8, 0};

@@ -703,21 +703,30 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
     }
 }
 
-// The sizes of M's groups for a launch in precision T.  The windows are
-// staged for FP64 operands where six workgroups' LDS fits a CU: FP32 gathers
-// (half the bytes) and groups with large dictionaries lose more by the lower
-// occupancy and the barrier (FP32 fine smoother of the 128^3 stack 25 us
-// staged, 20 us gathering; FP64 of the 96^3 cube 28 us and 25 us).  A launch of
-// fewer rows gathers too: its workgroups are all resident at once and staging is
-// one more step of their chain (FP64 smoothers gathering and staged: 15 thousand
-// rows of 27 entries 4.0 and 4.7 us, 27 thousand 4.2 and 5.2, 91 thousand 5.4
-// and 5.8; 118 thousand 5.9 and 5.7, 531 thousand 13.0 and 11.1).
+// The sizes of M's groups for a launch in precision T over `rows` rows of
+// `entries` entries in all.  The windows are staged for FP64 operands where six
+// workgroups' LDS fits a CU: FP32 gathers (half the bytes) and groups with large
+// dictionaries lose more by the lower occupancy and the barrier (FP32 fine
+// smoother of the 128^3 stack 25 us staged, 20 us gathering; FP64 of the 96^3 cube
+// 28 us and 25 us).  Staging is one more step of a workgroup's chain, which pays
+// where there are many gathers to spare: not in launches whose workgroups are all
+// resident at once, nor for short rows, at any number of them.  FP64 smoothers
+// gathering and staged, us:
+//   27 entries a row: 27 thousand rows 4.0, 4.4; 74 thousand 4.6, 4.9; 97 thousand
+//     5.5, 5.4; 262 thousand 8.6, 7.6; 2.1 million 40, 33
+//   19 and 21: 125 thousand rows 5.2, 5.4 and 5.1, 5.0; 262 thousand 7.3, 6.9 and
+//     7.4, 6.9; 2.1 million 34, 31 and 34, 32
+//   13 and 15: 262 thousand 5.9, 6.5 and 7.1, 7.5; 531 thousand (15) 9.7, 9.1;
+//     1 million equal
+//   7 and 9: 262 thousand 4.4, 5.5 and 5.3, 5.5; 490 thousand (9) 7.7, 7.6; 1 million
+//     (9) 13.2, 13.7; 4.2 million (9) 34, 38
 constexpr int kRowsStageLds = 160 * 1024 / 6;
-constexpr int kRowsStageRows = 100000;
+constexpr int64_t kRowsStageEntries = 2500000;
+constexpr int kRowsStageWidth = 16;
 template <typename T>
-inline RowsSize rows_size(int max_e, int max_n, int max_x, int dots, int rows) {
+inline RowsSize rows_size(int max_e, int max_n, int max_x, int dots, int64_t rows, int64_t entries) {
     RowsSize z{max_e, max_n, max_x, dots};
-    if (sizeof(T) == 4 || rows < kRowsStageRows ||
+    if (sizeof(T) == 4 || entries < kRowsStageEntries || entries < kRowsStageWidth * rows ||
         rows_lds<T>(RowsSize{max_e, max_n, max_x, 0}).bytes > kRowsStageLds)
         z.max_x = 0;
     return z;

@@ -58,6 +58,17 @@ def test_repeating_rows_have_dictionaries(shape, precision):
         h.close()
 
 
+# 9 entries a row at any size, 27 of them in few rows and in many
+@pytest.mark.parametrize("shape,staged", [((520, 510), False), ((720, 700), False), ((40, 40, 40), False), ((97, 81, 33), True)])
+def test_windows_are_staged_for_many_long_rows(shape, staged):
+    import paper_2602_05686_amd as amg
+
+    h = amg.Hierarchy.from_problem(_box(shape, "constant"), max_levels=16)
+    f = h.level_form(0)
+    assert f["dictionaries"] > 0 and bool(f["staged"]) == staged
+    h.close()
+
+
 @pytest.mark.parametrize("width,taken", [(12, True), (32, True), (33, False)])
 def test_dictionary_rows_are_those_one_thread_sums(width, taken):
     import paper_2602_05686_amd as amg
