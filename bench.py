@@ -21,6 +21,8 @@ in [32, 128], layered or anisotropic, FP32-hierarchy form, 8 GiB budget:
 p50 / p99 latency and solves/s, over all requests and over the converged
 ones) and the CPU oracle's full setup and solve of the same workload,
 measured on one host core, whose solution the GPU results are compared with.
+The line holds the main figures; --record FILE keeps all of them, the parameter
+studies' rows included (which stderr shows as they are measured).
 """
 
 import argparse
@@ -64,6 +66,59 @@ def measured_traffic():
         return float(kv["traffic_bytes_per_launch"])
     except (OSError, KeyError, ValueError):
         return None
+
+
+def _short(v):
+    """The same record with its numbers at six digits."""
+    if isinstance(v, dict):
+        return {k: _short(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [_short(x) for x in v]
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
+def _pick(v, *keys):
+    return None if v is None else {k: v[k] for k in keys if k in v}
+
+
+def headline(record):
+    """The record's line on stdout: the timed result in full, of the other parts their main figures, a few kilobytes
+    in all (the studies alone are some 150 KB, more than a log of the last lines keeps)."""
+    line = {k: record[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+                                   "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config")}
+    line.update(_short(_pick(record, "solve_only_dof_per_s", "t_setup_ms", "t_solve_ms", "step_ms_stats",
+                             "iterations_per_step", "iterations", "rel_res_true", "rel_err_vs_closed_form", "seeded_x0",
+                             "levels", "op_complexity", "vcycle", "roofline")))
+
+    def form(f):
+        out = _pick(f, "status", "iterations", "rel_res", "dof_per_s", "solve_only_dof_per_s", "t_setup_ms", "t_solve_s",
+                    "rel_err_vs_closed_form")
+        if out is not None:
+            for k in ("t_setup_ms_stats", "t_solve_ms_stats"):
+                if k in f:
+                    out[k[:-6] + "_median"] = f[k]["median"]
+            out["vcycle"] = _pick(f["vcycle"], "ms", "alg_GBps", "fine_smoother_us")
+        return out
+
+    fp32 = record["fp32_form"]
+    if fp32 is not None:
+        line["fp32_form"] = _short({**form(fp32), **_pick(fp32, "speedup_vs_fp64_solve", "speedup_per_iteration",
+                                                           "speedup_vs_fp64_vcycle", "rel_err_vs_fp64_form")})
+        if fp32.get("aniso"):
+            a = fp32["aniso"]
+            line["fp32_form"]["aniso"] = _short({k: form(v) if isinstance(v, dict) and "vcycle" in v else v
+                                                 for k, v in a.items()})
+    c4 = record["layered192"]
+    if c4 is not None:
+        line["layered192"] = _short({k: form(v) if isinstance(v, dict) else v for k, v in c4.items()})
+    line["serving"] = _short(_pick(record["serving"], "requests", "rate_per_s", "budget_GiB", "p50_latency_s",
+                                   "p99_latency_s", "solves_per_s", "served_dof_per_s", "makespan_s", "status_counts",
+                                   "converged_only", "mean_batch", "max_batch", "rounds", "launches",
+                                   "peak_reserved_GiB", "estimate_exceeded", "failed"))
+    line["cpu_baseline"] = _short(record["cpu_baseline"])
+    if record["studies"] is not None:
+        line["studies"] = {k: f"{len(v['rows'])} rows" for k, v in record["studies"].items()}
+    return line
 
 
 def cpu_model():
@@ -676,6 +731,7 @@ def main():
                     help="run only the setup-reuse measurement (material update, successive right-hand sides)")
     ap.add_argument("--reuse-rhs", type=int, default=16)
     ap.add_argument("--reuse-max-iter", type=int, default=1000)
+    ap.add_argument("--record", default=None, metavar="FILE", help="write the full record, of which the line holds the main figures, to FILE")
     ap.add_argument("--serve-num", type=int, default=256)
     ap.add_argument("--serve-rate", type=float, default=20.0)
     ap.add_argument("--serve-budget-gib", type=float, default=8.0)
@@ -922,7 +978,10 @@ def main():
         "studies": studies,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(out), flush=True)
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(headline(out)), flush=True)
 
 
 if __name__ == "__main__":
