@@ -68,6 +68,13 @@ def measured_traffic():
         return None
 
 
+def smoother_kernel(form):
+    """The kernel that a level's smoother steps launch, of a matrix read in the given form (Hierarchy.level_form)."""
+    if form["dictionaries"] > 0:
+        return "k_rows<double, SMOOTH>"
+    return f"k_stream<double, SMOOTH, {form['threads_per_row']} thread(s) per row, {form['block_entries']} entries>"
+
+
 def _short(v):
     """The same record with its numbers at six digits."""
     if isinstance(v, dict):
@@ -847,6 +854,7 @@ def main():
     t_vc_ms = time_vcycles(h, n, args.vcycles, dev)
     vc_gbs = st["vcycle_alg_bytes"] / (t_vc_ms * 1e-3) / 1e9
     kt = h.time_smoother(level=0, reps=args.vcycles)
+    kernel = smoother_kernel(h.level_form(0))
     avg_ms = kt["avg_ms"]
     achieved = kt["bytes_per_launch"] / (avg_ms * 1e-3) / 1e9
     log(f"V-cycle {t_vc_ms:.3f} ms = {vc_gbs:.0f} GB/s algorithmic; fine smoother SpMV {avg_ms * 1e3:.1f} us "
@@ -965,7 +973,7 @@ def main():
         "op_complexity": st["op_complexity"],
         "vcycle": {"ms": t_vc_ms, "alg_bytes": st["vcycle_alg_bytes"], "alg_GBps": vc_gbs,
                    "frac_of_peak": vc_gbs / HBM_PEAK_GBS},
-        "roofline": {"bound": "hbm", "kernel": "fused FP64 Chebyshev SpMV on the finest level (k_rows<double, SMOOTH>)",
+        "roofline": {"bound": "hbm", "kernel": f"fused FP64 Chebyshev SpMV on the finest level ({kernel})",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic, "avg_launch_us": avg_ms * 1e3, "launches": args.vcycles,
                      "alg_bytes_per_launch": kt["bytes_per_launch"],

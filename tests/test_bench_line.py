@@ -73,3 +73,12 @@ def test_line_of_a_partial_run():
     rec = dict(_record(), fp32_form=None, layered192=None, serving=None, studies=None, cpu_baseline=None, seeded_x0=None)
     got = json.loads(json.dumps(bench.headline(rec)))
     assert all(got[k] == rec[k] for k in CONTRACT) and got["serving"] is None
+
+
+def test_roofline_names_the_kernel_that_ran():
+    import bench
+
+    form = dict(threads_per_row=1, block_entries=4096, blocks=1, columns="16-bit", windowed_entries=0, dictionaries=7,
+                staged=1, one_workgroup=0)
+    assert "k_rows" in bench.smoother_kernel(form)
+    assert "k_stream" in bench.smoother_kernel(dict(form, dictionaries=0))
