@@ -41,11 +41,19 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kHS = 1024;     // LDS hash slots per wave
 constexpr int kDMax = 512;    // max distinct columns on the LDS path
 // numeric phase: distinct columns of a row (at most) and LDS hash slots per
-// wavefront, in three sizes, so that a CU holds 8, 7 and 3 workgroups
+// wavefront, in three sizes, of which a CU's LDS holds 8 or more, 6 and 3
+// workgroups
 constexpr int kNumCols[3] = {128, 256, kDMax};
 constexpr int kNumSlots[3] = {256, 384, 768};
 // parts of a row's column range in rank_columns, for rows of up to d columns
 constexpr int rank_parts(int d) { return d / 4; }
+// LDS of a workgroup: keys, running sums, columns' list and parts (see k_spgemm_numeric)
+constexpr int num_lds(int i) {
+    return kWaves * ((int)(sizeof(int) + sizeof(double)) * kNumSlots[i] +
+                     (int)sizeof(int) * (kNumCols[i] + rank_parts(kNumCols[i]) + 1));
+}
+constexpr int kCuLds = 160 * 1024;
+static_assert(kCuLds / num_lds(0) >= 8 && kCuLds / num_lds(1) == 6 && kCuLds / num_lds(2) == 3);
 // lists of fewer rows leave out the middle size (a launch of 4 us)
 constexpr int kNumThreeSizes = 32768;
 constexpr int kRankTile = 1024;  // LDS tile of the column list when ranking long rows
@@ -60,7 +68,7 @@ constexpr int kHSBig = 9216;     // their LDS hash slots
 // dynamic LDS of the large-table workgroup: a key and a running sum per slot,
 // and the columns' list and parts
 constexpr size_t kBigLds = (sizeof(int) + sizeof(double)) * kHSBig + sizeof(int) * (kDBig + rank_parts(kDBig) + 1);
-static_assert(kBigLds + 1024 <= 160 * 1024, "the large table fits a CU");
+static_assert(kBigLds + 1024 <= kCuLds, "the large table fits a CU");
 // numeric phase of the wavefront path: LDS table per wavefront (rows of at
 // most kDMax columns) or global-memory table (overflow rows of more than
 // kDBig columns); the overflow rows in between take numeric_row_big
