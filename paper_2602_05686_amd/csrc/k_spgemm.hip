@@ -69,10 +69,6 @@ constexpr int kHSBig = 9216;     // their LDS hash slots
 // and the columns' list and parts
 constexpr size_t kBigLds = (sizeof(int) + sizeof(double)) * kHSBig + sizeof(int) * (kDBig + rank_parts(kDBig) + 1);
 static_assert(kBigLds + 1024 <= kCuLds, "the large table fits a CU");
-// numeric phase of the wavefront path: LDS table per wavefront (rows of at
-// most kDMax columns) or global-memory table (overflow rows of more than
-// kDBig columns); the overflow rows in between take numeric_row_big
-enum NumericMode { N_LDS = 0, N_GLOBAL = 1 };
 
 __device__ __forceinline__ unsigned hash_slot(int key, unsigned mask) {
     return ((unsigned)key * 2654435761u) & mask;
@@ -364,18 +360,12 @@ __device__ __forceinline__ void phase_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-template <bool GLOBAL>
-__device__ __forceinline__ int key_at(const int* keys, unsigned h) {
-    if constexpr (GLOBAL) return ld_key(keys + h);
-    else return keys[h];
-}
-
-// slot of a key known to be present; the probe count is bounded by the table size
-template <bool GLOBAL>
+// slot of a key known to be present in a global-memory table; the probe count
+// is bounded by the table size
 __device__ __forceinline__ unsigned hash_find_fresh(const int* keys, unsigned mask, int key) {
     unsigned h = hash_slot(key, mask);
     for (unsigned probe = 0; probe <= mask; ++probe) {
-        if (key_at<GLOBAL>(keys, h) == key) return h;
+        if (ld_key(keys + h) == key) return h;
         h = (h + 1) & mask;
     }
     return 0;
@@ -437,161 +427,137 @@ __global__ __launch_bounds__(kBlock) void k_spgemm_symbolic(int nrows, const int
                              skeys[GLOBAL ? 0 : w]);
 }
 
-// row i (list position ridx) of the numeric phase, by one wavefront
-template <int MODE, int HS, int DM>
-__device__ void numeric_row(int ridx, int i, const int* arp, const int* acol, const double* aval, const int* brp,
-                            const int* bcol, const double* bval, const int* crp, int* ccol, double* cval, int* gkeys,
-                            int* gvals, double* gacc, const int64_t* goff, int mlo, int* lds_keys, int* lds_vals,
-                            double* lds_acc, int* lds_tile) {
-    constexpr bool GLOBAL = MODE == N_GLOBAL;
+// Row i of the numeric phase, by one wavefront on its LDS table of at most HS
+// slots (rows of at most DM columns).  One walk over the products: each takes
+// its column's hash slot (inserting the column on first sight) and is added to
+// that slot's running sum in canonical order, the segments of a step one after
+// the other; then the occupied slots are ranked by column and written out.
+// Every entry receives the same additions in the same order as in the two walks
+// of numeric_row_global (a zeroed sum plus the first product, then the others).
+template <int HS, int DM>
+__device__ void numeric_row_lds(int i, const int* arp, const int* acol, const double* aval, const int* brp,
+                                const int* bcol, const double* bval, const int* crp, int* ccol, double* cval, int* keys,
+                                int* vals, double* acc) {
     const int lane = threadIdx.x & 63;
-    // overflow rows of up to mlo columns take the large LDS table
-    if (GLOBAL && crp[i + 1] - crp[i] <= mlo) return;
-    int *keys, *vals;
-    double* acc;
-    unsigned mask;
-    if (GLOBAL) {
-        const int64_t o = goff[ridx];
-        keys = gkeys + o;
-        vals = gvals + o;
-        acc = gacc + o;
-        mask = (unsigned)(goff[ridx + 1] - o) - 1;
-    } else {
-        keys = lds_keys;
-        vals = lds_vals;
-        acc = lds_acc;
-        mask = 0;
+    const int base = crp[i];
+    const int d = crp[i + 1] - base;
+    const unsigned slots = lds_slots(d, HS);
+    for (unsigned h = lane; h < slots; h += 64) {
+        keys[h] = -1;
+        acc[h] = 0.0;
     }
-    if constexpr (MODE == N_LDS) {
-        const unsigned slots = lds_slots(crp[i + 1] - crp[i], HS);
-        // One walk over the products: each takes its column's hash slot
-        // (inserting the column on first sight) and is added to that slot's
-        // running sum in canonical order, the segments of a step one after
-        // the other; then the occupied slots are ranked by column and written
-        // out.  Every entry receives the same additions in the
-        // same order as on the two-walk path (a zeroed sum plus the first
-        // product, then the others).
-        for (unsigned h = lane; h < slots; h += 64) {
-            keys[h] = -1;
-            acc[h] = 0.0;
+    phase_fence<false>();
+    for_each_product<true>(arp, acol, aval, brp, bcol, bval, i,
+                           [&](bool valid, int c, double pv, int t0, int total, int seg) {
+                               bool fresh;
+                               const unsigned h = valid ? lds_insert(keys, slots, c, fresh) : 0u;
+                               add_segments(acc, valid, h, pv, seg, lane_int(seg, 0),
+                                            lane_int(seg, min(64, total - t0) - 1));
+                               return true;
+                           });
+    phase_fence<false>();
+    if (d <= 64) {
+        // a lane per column, compared with all
+        int filled = 0, h = 0;
+        for (unsigned h0 = 0; h0 < slots; h0 += 64) {
+            const bool occ = h0 + lane < slots && keys[h0 + lane] >= 0;
+            const uint64_t bal = __ballot(occ);
+            if (occ) vals[filled + __popcll(bal & ((1ull << lane) - 1ull))] = (int)h0 + lane;
+            filled += __popcll(bal);
         }
         phase_fence<false>();
-        for_each_product<true>(arp, acol, aval, brp, bcol, bval, i,
-                               [&](bool valid, int c, double pv, int t0, int total, int seg) {
-                                   bool fresh;
-                                   const unsigned h = valid ? lds_insert(keys, slots, c, fresh) : 0u;
-                                   add_segments(acc, valid, h, pv, seg, lane_int(seg, 0),
-                                                lane_int(seg, min(64, total - t0) - 1));
-                                   return true;
-                               });
-        phase_fence<false>();
-        const int base = crp[i];
-        const int d = crp[i + 1] - base;
-        if (d <= 64) {
-            // a lane per column, compared with all
-            int filled = 0, h = 0;
-            for (unsigned h0 = 0; h0 < slots; h0 += 64) {
-                const bool occ = h0 + lane < slots && keys[h0 + lane] >= 0;
-                const uint64_t bal = __ballot(occ);
-                if (occ) vals[filled + __popcll(bal & ((1ull << lane) - 1ull))] = (int)h0 + lane;
-                filled += __popcll(bal);
-            }
-            phase_fence<false>();
-            int key = 0x7fffffff;
-            if (lane < d) {
-                h = vals[lane];
-                key = keys[h];
-            }
-            int r = 0;
-            for (int q = 0; q < d; ++q) r += lane_int(key, q) < key ? 1 : 0;
-            if (lane < d) {
-                ccol[base + r] = key;
-                cval[base + r] = acc[h];
-            }
-            phase_fence<false>();
-            return;
+        int key = 0x7fffffff;
+        if (lane < d) {
+            h = vals[lane];
+            key = keys[h];
         }
+        int r = 0;
+        for (int q = 0; q < d; ++q) r += lane_int(key, q) < key ? 1 : 0;
+        if (lane < d) {
+            ccol[base + r] = key;
+            cval[base + r] = acc[h];
+        }
+    } else {
         rank_columns<64>(keys, slots, d, vals, vals + DM, rank_parts(DM), nullptr, lane, [] { phase_fence<false>(); },
                          [&](int h, int key, int r) {
                              ccol[base + r] = key;
                              cval[base + r] = acc[h];
                          });
-        phase_fence<false>();  // the tables are reused by the wavefront's next row
-        return;
     }
+    phase_fence<false>();  // the tables are reused by the wavefront's next row
+}
+
+// Overflow row i (list position ridx) of more columns than any LDS table takes,
+// by one wavefront on its table in global memory: the columns are ranked first,
+// then the products are accumulated by rank in a second walk.
+__device__ void numeric_row_global(int ridx, int i, const int* arp, const int* acol, const double* aval, const int* brp,
+                                   const int* bcol, const double* bval, const int* crp, int* ccol, double* cval,
+                                   int* gkeys, int* gvals, double* gacc, const int64_t* goff, int* tile) {
+    const int lane = threadIdx.x & 63;
+    const int64_t o = goff[ridx];
+    int *keys = gkeys + o, *vals = gvals + o;
+    double* acc = gacc + o;
+    const unsigned mask = (unsigned)(goff[ridx + 1] - o) - 1;
     for (unsigned h = lane; h <= mask; h += 64) {
         keys[h] = -1;
         vals[h] = 0;
     }
-    phase_fence<GLOBAL>();
+    phase_fence<true>();
     for_each_product<false>(arp, acol, nullptr, brp, bcol, nullptr, i,
                             [&](bool valid, int c, double, int, int, int) {
                                 if (valid) (void)hash_insert(keys, mask, c);
                                 return true;
                             });
-    phase_fence<GLOBAL>();
-    // compact the occupied slots (arbitrary order): into LDS on the LDS path
-    // (the accumulator's space, unused until the ranks are known), into the
-    // output column range otherwise
+    phase_fence<true>();
+    // compact the occupied slots (arbitrary order) into the output column range
     const int base = crp[i];
     const int d = crp[i + 1] - base;
     int* cl = ccol + base;
-    int* lst = GLOBAL ? cl : reinterpret_cast<int*>(acc);
     int filled = 0;
     for (unsigned h0 = 0; h0 <= mask; h0 += 64) {
         const unsigned h = h0 + lane;
-        const int key = (h <= mask) ? key_at<GLOBAL>(keys, h) : -1;
+        const int key = (h <= mask) ? ld_key(keys + h) : -1;
         const bool occ = key >= 0;
         const uint64_t bal = __ballot(occ);
         const int before = __popcll(bal & ((1ull << lane) - 1ull));
-        if (occ && filled + before < d) lst[filled + before] = key;
+        if (occ && filled + before < d) cl[filled + before] = key;
         filled += __popcll(bal);
     }
-    phase_fence<GLOBAL>();
-    // rank of each column among the row's columns = its output position
-    if constexpr (MODE == N_LDS) {
-        for (int e = lane; e < d; e += 64) {
-            const int c = lst[e];
-            int r = 0;
-            for (int q = 0; q < d; ++q) r += (lst[q] < c);
-            vals[hash_find_fresh<GLOBAL>(keys, mask, c)] = r;
+    phase_fence<true>();
+    // rank of each column among the row's columns = its output position:
+    // kRankKeys keys per lane at a time, compared against the list staged
+    // through LDS in tiles
+    for (int e0 = 0; e0 < d; e0 += 64 * kRankKeys) {
+        int c[kRankKeys], r[kRankKeys];
+#pragma unroll
+        for (int u = 0; u < kRankKeys; ++u) {
+            const int e = e0 + u * 64 + lane;
+            c[u] = e < d ? cl[e] : -1;
+            r[u] = 0;
         }
-    } else {
-        // long rows: kRankKeys keys per lane at a time, compared against the
-        // list staged through LDS in tiles
-        int* tile = lds_tile;
-        for (int e0 = 0; e0 < d; e0 += 64 * kRankKeys) {
-            int c[kRankKeys], r[kRankKeys];
+        for (int t0 = 0; t0 < d; t0 += kRankTile) {
+            const int tn = min(kRankTile, d - t0);
+            for (int q = lane; q < tn; q += 64) tile[q] = cl[t0 + q];
+            phase_fence<false>();
+            for (int q = 0; q < tn; ++q) {
+                const int v = tile[q];
 #pragma unroll
-            for (int u = 0; u < kRankKeys; ++u) {
-                const int e = e0 + u * 64 + lane;
-                c[u] = e < d ? lst[e] : -1;
-                r[u] = 0;
+                for (int u = 0; u < kRankKeys; ++u) r[u] += (v < c[u]) ? 1 : 0;
             }
-            for (int t0 = 0; t0 < d; t0 += kRankTile) {
-                const int tn = min(kRankTile, d - t0);
-                for (int q = lane; q < tn; q += 64) tile[q] = lst[t0 + q];
-                phase_fence<false>();
-                for (int q = 0; q < tn; ++q) {
-                    const int v = tile[q];
-#pragma unroll
-                    for (int u = 0; u < kRankKeys; ++u) r[u] += (v < c[u]) ? 1 : 0;
-                }
-                phase_fence<false>();
-            }
-#pragma unroll
-            for (int u = 0; u < kRankKeys; ++u)
-                if (c[u] >= 0) vals[hash_find_fresh<GLOBAL>(keys, mask, c[u])] = r[u];
+            phase_fence<false>();
         }
+#pragma unroll
+        for (int u = 0; u < kRankKeys; ++u)
+            if (c[u] >= 0) vals[hash_find_fresh(keys, mask, c[u])] = r[u];
     }
-    phase_fence<GLOBAL>();
+    phase_fence<true>();
     for (unsigned h = lane; h <= mask; h += 64) {
-        const int key = key_at<GLOBAL>(keys, h);
+        const int key = ld_key(keys + h);
         const int r = vals[h];
         if (key >= 0 && r >= 0 && r < d) cl[r] = key;
     }
     for (int e = lane; e < d; e += 64) acc[e] = 0.0;
-    phase_fence<GLOBAL>();
+    phase_fence<true>();
     // Accumulate in canonical product order.  The products of one A entry
     // (a segment) have distinct columns, so a segment's lanes add their
     // products to their columns' running values at once; the segments of a
@@ -600,58 +566,68 @@ __device__ void numeric_row(int ridx, int i, const int* arp, const int* acol, co
     // additions of a serial row product.
     for_each_product<true>(arp, acol, aval, brp, bcol, bval, i,
                            [&](bool valid, int c, double pv, int t0, int total, int seg) {
-                               int r = valid ? vals[hash_find_fresh<GLOBAL>(keys, mask, c)] : 0;
+                               int r = valid ? vals[hash_find_fresh(keys, mask, c)] : 0;
                                r = (r >= 0 && r < d) ? r : 0;
                                const int m = min(64, total - t0);
                                const int s0 = __shfl(seg, 0, 64), s1 = __shfl(seg, m - 1, 64);
                                for (int sg = s0; sg <= s1; ++sg) {
                                    if (valid && seg == sg) acc[r] += pv;
-                                   phase_fence<GLOBAL>();
+                                   phase_fence<true>();
                                }
                                return true;
                            });
-    phase_fence<GLOBAL>();
+    phase_fence<true>();
     for (int e = lane; e < d; e += 64) cval[base + e] = acc[e];
 }
 
-// LDS path (N_LDS): the rows of the list whose distinct column count lies in
-// (mlo, mhi] (known from the symbolic phase: rows of many products but few
-// columns take the small tables) and that did not overflow (skip), with HS
-// hash slots and room for DM = mhi columns per wave; N_GLOBAL: the listed overflow rows with
-// more than mlo (at most kDBig) columns.  A wavefront per row, grid-stride
-// over runs of up to eight rows whose counts its lanes read together (one row
-// after the other, the rows that are not this launch's cost a memory latency
-// each); nrows_dev (if set) holds the count.
-template <int MODE, int HS, int DM>
+// The rows of the list whose distinct column count lies in (mlo, mhi] (known
+// from the symbolic phase: rows of many products but few columns take the small
+// tables) and that did not overflow (skip), with HS hash slots and room for DM =
+// mhi columns per wavefront.  A wavefront per row, grid-stride over runs of up to
+// eight rows whose counts its lanes read together (one row after the other, the
+// rows that are not this launch's cost a memory latency each); nrows_dev (if set)
+// holds the count.
+template <int HS, int DM>
 __global__ __launch_bounds__(kBlock) void k_spgemm_numeric(int nrows, const int* nrows_dev, const int* rows,
                                                            const int* arp, const int* acol, const double* aval,
                                                            const int* brp, const int* bcol, const double* bval,
                                                            const int* crp, int* ccol, double* cval, const int* skip,
-                                                           int* gkeys, int* gvals, double* gacc,
-                                                           const int64_t* goff, int mlo, int mhi) {
-    constexpr bool GLOBAL = MODE == N_GLOBAL;
-    __shared__ __align__(16) int skeys[GLOBAL ? 1 : kWaves][GLOBAL ? 4 : HS];
-    __shared__ int svals[GLOBAL ? 1 : kWaves][GLOBAL ? 1 : DM + rank_parts(DM) + 1];  // see rank_columns
-    __shared__ double sacc[GLOBAL ? 1 : kWaves][GLOBAL ? 1 : HS];  // one running sum per hash slot
-    __shared__ int stile[GLOBAL ? kWaves : 1][GLOBAL ? kRankTile : 1];
+                                                           int mlo, int mhi) {
+    __shared__ __align__(16) int skeys[kWaves][HS];
+    __shared__ int svals[kWaves][DM + rank_parts(DM) + 1];  // see rank_columns
+    __shared__ double sacc[kWaves][HS];                     // one running sum per hash slot
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int nr = nrows_dev ? *nrows_dev : nrows;
     const int waves = (int)gridDim.x * kWaves;
-    const int take = GLOBAL ? 1 : max(1, min(8, nr / waves));
+    const int take = max(1, min(8, nr / waves));
     for (int first = (blockIdx.x * kWaves + w) * take; first < nr; first += waves * take) {
         int row = 0;
         bool mine = false;
         if (lane < take && first + lane < nr) {
             row = rows ? rows[first + lane] : first + lane;
             const int dc = crp[row + 1] - crp[row];
-            mine = GLOBAL || (dc > mlo && dc <= mhi && !(skip && skip[row]));
+            mine = dc > mlo && dc <= mhi && !(skip && skip[row]);
         }
-        for (unsigned long long left = __ballot(mine); left; left &= left - 1ull) {
-            const int l = __builtin_ctzll(left);
-            numeric_row<MODE, HS, DM>(first + l, lane_int(row, l), arp, acol, aval, brp, bcol, bval, crp, ccol, cval, gkeys,
-                                  gvals, gacc, goff, mlo, skeys[GLOBAL ? 0 : w], svals[GLOBAL ? 0 : w],
-                                  sacc[GLOBAL ? 0 : w], stile[GLOBAL ? w : 0]);
-        }
+        for (unsigned long long left = __ballot(mine); left; left &= left - 1ull)
+            numeric_row_lds<HS, DM>(lane_int(row, __builtin_ctzll(left)), arp, acol, aval, brp, bcol, bval, crp, ccol,
+                                    cval, skeys[w], svals[w], sacc[w]);
+    }
+}
+
+// the listed overflow rows of more than mlo columns (the others take the large
+// LDS table), a wavefront per row
+__global__ __launch_bounds__(kBlock) void k_spgemm_numeric_global(int nrows, const int* rows, const int* arp,
+                                                                  const int* acol, const double* aval, const int* brp,
+                                                                  const int* bcol, const double* bval, const int* crp,
+                                                                  int* ccol, double* cval, int* gkeys, int* gvals,
+                                                                  double* gacc, const int64_t* goff, int mlo) {
+    __shared__ int stile[kWaves][kRankTile];
+    const int w = threadIdx.x >> 6;
+    for (int ridx = blockIdx.x * kWaves + w; ridx < nrows; ridx += gridDim.x * kWaves) {
+        const int i = rows[ridx];
+        if (crp[i + 1] - crp[i] > mlo)
+            numeric_row_global(ridx, i, arp, acol, aval, brp, bcol, bval, crp, ccol, cval, gkeys, gvals, gacc, goff,
+                               stile[w]);
     }
 }
 
@@ -1030,7 +1006,6 @@ struct Route {
     int tprod = kThreadProducts, dmax = kDMax, dbig = kDBig;
 };
 
-//
 // The thread route is left out where the device has threads to spare: its
 // rows are chains of dependent loads and compares, about 100 us a kernel
 // however few they are (A P of 6,400 rows 371 us, 43 us with a wavefront
@@ -1145,12 +1120,11 @@ void spgemm(const DCsr& A, const DCsr& B, DCsr& C, MemCounter* mc, hipStream_t s
         auto numeric = [&](auto kernel, int mlo, int mhi) {
             hipLaunchKernelGGL(kernel, dim3(wgrid), dim3(kBlock), 0, s, n, nwide_dev, wlist, A.rowptr.get(),
                                A.col.get(), A.val.get(), B.rowptr.get(), B.col.get(), B.val.get(), C.rowptr.get(),
-                               C.col.get(), C.val.get(), (const int*)flags.get(), (int*)nullptr, (int*)nullptr,
-                               (double*)nullptr, (const int64_t*)nullptr, mlo, mhi);
+                               C.col.get(), C.val.get(), (const int*)flags.get(), mlo, mhi);
         };
-        numeric(k_spgemm_numeric<N_LDS, kNumSlots[0], kNumCols[0]>, -1, kNumCols[0]);
-        if (n >= kNumThreeSizes) numeric(k_spgemm_numeric<N_LDS, kNumSlots[1], kNumCols[1]>, kNumCols[0], kNumCols[1]);
-        numeric(k_spgemm_numeric<N_LDS, kNumSlots[2], kNumCols[2]>, n >= kNumThreeSizes ? kNumCols[1] : kNumCols[0],
+        numeric(k_spgemm_numeric<kNumSlots[0], kNumCols[0]>, -1, kNumCols[0]);
+        if (n >= kNumThreeSizes) numeric(k_spgemm_numeric<kNumSlots[1], kNumCols[1]>, kNumCols[0], kNumCols[1]);
+        numeric(k_spgemm_numeric<kNumSlots[2], kNumCols[2]>, n >= kNumThreeSizes ? kNumCols[1] : kNumCols[0],
                 kNumCols[2]);
         MATAMG_LAUNCH_CHECK();
     }
@@ -1166,10 +1140,10 @@ void spgemm(const DCsr& A, const DCsr& B, DCsr& C, MemCounter* mc, hipStream_t s
                            (const int*)list.get(), A.rowptr.get(), A.col.get(), A.val.get(), B.rowptr.get(),
                            B.col.get(), B.val.get(), (const int*)C.rowptr.get(), C.col.get(), C.val.get(),
                            route.dbig);
-        hipLaunchKernelGGL((k_spgemm_numeric<N_GLOBAL, 1, 1>), dim3(ceil_div(novf, kWaves)), dim3(kBlock), 0, s, novf,
-                           (const int*)nullptr, list.get(), A.rowptr.get(), A.col.get(), A.val.get(), B.rowptr.get(),
-                           B.col.get(), B.val.get(), C.rowptr.get(), C.col.get(), C.val.get(), (const int*)nullptr,
-                           gkeys.get(), gvals.get(), gacc.get(), toff.get(), route.dbig, 0);
+        hipLaunchKernelGGL(k_spgemm_numeric_global, dim3(ceil_div(novf, kWaves)), dim3(kBlock), 0, s, novf,
+                           (const int*)list.get(), A.rowptr.get(), A.col.get(), A.val.get(), B.rowptr.get(), B.col.get(),
+                           B.val.get(), (const int*)C.rowptr.get(), C.col.get(), C.val.get(), gkeys.get(), gvals.get(),
+                           gacc.get(), (const int64_t*)toff.get(), route.dbig);
         MATAMG_LAUNCH_CHECK();
     }
     // no synchronisation: temporaries go back to the pool in stream order
