@@ -11,8 +11,16 @@
 
 namespace matamg {
 
-// Upper bound of the device bytes one request holds while its hierarchy is
-// built (the setup peak), from the fine-level sizes.  Per stored entry of A:
+// Estimate of the device bytes one request holds while its hierarchy is built
+// (the setup peak), from the fine-level sizes: what the first level takes, plus
+// the dense coarse solve.  Not a bound: the coarser levels are known only once
+// they are built.  Those of layered stacks and anisotropic cubes, and their row
+// dictionaries (up to 4 B an entry and 14 B a row) and column windows (2 B an entry
+// and 48 B a row block), fit in what the first level's filtered matrix, strength
+// numerators and products have given back by then: their setups peak at 0.15 to
+// 0.8 of the estimate.  Cubes of one random coefficient per element coarsen
+// slowly and peak at 1.3 to 2.3 times it; the server counts such setups
+// (estimate_exceeded).  Per stored entry of A:
 // the matrix (12 B), strength values and drop mask (9 B), the strength
 // numerators during the drop (8 B), the filtered matrix (12 B), the FP32
 // copies (4 B), the SpGEMM products of the first level (bounded by 12 B) and

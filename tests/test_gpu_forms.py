@@ -147,6 +147,31 @@ def test_levels_with_long_rows_keep_their_launches(n, max_coarse, precision):
     h.close()
 
 
+# a request whose finest rows have dictionaries, and two with windows
+@pytest.mark.parametrize("name", ["stack", "ring", "wide"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_admission_estimate_covers_the_forms(name, precision):
+    import types
+
+    import paper_2602_05686_amd as amg
+    from workloads import layered_stack_3d
+
+    kw = dict(precision=precision, max_levels=16)
+    if name == "stack":
+        p = layered_stack_3d(n=48, repeats=16)
+    else:
+        n, parts, hubs = windows._CASES[name]
+        a = windows._matrix(n, parts, hubs, np.random.default_rng(11))
+        p = types.SimpleNamespace(n=n, dim=1, rowptr=a.indptr.astype(np.int32), col=a.indices.astype(np.int32), val=a.data,
+                                  elem_nodes=np.zeros((0, 2), np.int32), elem_sigma=np.zeros((0, 1, 1)),
+                                  coords=np.arange(n, dtype=np.float64)[:, None], b=np.ones(n))
+        kw.update(soc="sa", theta=0.0)
+    with amg.Server(budget_bytes=8 << 30, dim=p.dim, **kw) as srv:
+        _, _, timeline = srv.result(tail._done(srv, srv.submit(p, max_iter=3)))
+        assert 0 < timeline["resident_bytes"] <= timeline["setup_peak_bytes"] <= timeline["est_bytes"]
+        assert srv.stats()["estimate_exceeded"] == 0
+
+
 def _csr(rcv, shape):
     import scipy.sparse as sp
 
