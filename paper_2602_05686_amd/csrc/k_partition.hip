@@ -12,9 +12,9 @@
 // once more, from its own entry, for the starts.  The result equals the host
 // walk exactly.  Launches are what bounds it on small matrices and memory
 // passes on large ones: five launches, three for a single chunk (radix-8
-// pointer jumping over marks, with scans, took about twenty, and the setup of the
-// 128^2 two-domain problem 5.6 ms, now 4.2 ms; of the 128^3 stack 34.8 and
-// 32.2 ms).
+// pointer jumping over marks, with scans, took about twenty; without it the setup
+// of the 128^2 two-domain problem went from 5.6 to 4.2 ms, of the 128^3 stack from
+// 34.8 to 32.2 ms).
 #include <algorithm>
 
 #include "device_util.h"

@@ -290,8 +290,9 @@ namespace {
 // leading scalar arguments are in registers when a wavefront starts, while the
 // rest of the arguments is itself a load, which then runs beside the tables'
 // (the kernels of small levels are a chain of four or five memory latencies,
-// 3.5 to 5 us in all: a V-cycle of the 512^2 two-domain problem, 39 launches,
-// 187 -> 179 us).  No more than these: each argument also costs the host.
+// 3.5 to 5 us in all: V-cycles of the 512^2 two-domain problem, 26 launches, 162 us
+// with all arguments loaded and 155 us so, of the 37 x 23 x 29 cube in FP32 64 and
+// 60 us).  No more than these: each argument also costs the host.
 template <typename T, int MODE, bool HAS_DOT, int G, int CAP = kStreamCap>
 __global__ __launch_bounds__(kBlock) void k_stream(const int* blk, const int* blkk, int nblk, SArgs<T> a) {
     __shared__ StreamShared<T, CAP> S;

@@ -388,10 +388,10 @@ __device__ __forceinline__ void stream_block(const SArgs<T>& a, int bid, StreamS
         // operands.  With G > 1 a group has rows_per_group(G) rows, kBlock / G
         // apart, and its thread q those of the q-th, so that none of these
         // loads waits behind the reduction and the epilogues are one pass of
-        // the group (its first thread, with all four rows' operands in 98
-        // registers, took four: FP64 smoother of the 192^3 stack's levels 2 to
-        // 4 226, 165 and 81 us, now 204, 148 and 72 us, of the 96^3 cube's
-        // level 2 22 and 19 us)
+        // the group (by its first thread alone, with all four rows' operands
+        // in 98 registers, they are four: FP64 smoother of the 192^3 stack's
+        // levels 2 to 4 226, 165 and 81 us against 204, 148 and 72 us, of the
+        // 96^3 cube's level 2 22 against 19 us)
         constexpr int RQ = G == 1 ? 1 : rows_per_group(G);
         const int gl = (int)threadIdx.x % G;
         const int r = r0 + (int)threadIdx.x / G + (gl % RQ) * (kBlock / G);
@@ -604,11 +604,15 @@ __device__ __forceinline__ T row_sum(const T* lv, int k0, int len, X x) {
 // gather from a few windows of consecutive columns (three planes of a mesh,
 // say), read once.  A row block's dot terms are summed in the streaming
 // kernel's order (its rows over four wavefronts, each by the wavefront tree,
-// the four sums in order).  What bounds it is the cache path of the gathers:
-// the FP64 fine smoother of the 128^3 stack takes 33 us for the 103 MB of its
-// vectors (staged; 41 us gathering), against 116 us from values and columns,
-// that of the 96^3 cube 25 us (gathering) against 52 us, and the FP32 ones 20
-// and 12 us against 72 and 30 us.
+// the four sums in order).  What bounds it where it gathers is the cache path: the
+// texture address units are busy 84% of the time (FP64, 96^3 cube) and 76% (FP32,
+// 128^3 stack).  Staged, no unit is (128^3 stack: vector units 52%, address units
+// 50%, LDS 45%, HBM at half the rate of a plain read): a workgroup's steps -- the
+// windows, the barrier, the sums -- follow one another, and a CU's LDS has room
+// for six workgroups to fill the gaps.  The FP64 fine smoother of the 128^3 stack
+// takes 33 us for the 103 MB of its vectors (staged; 41 us gathering), against 116
+// us from values and columns, that of the 96^3 cube 24 us (gathering) against 52
+// us, and the FP32 ones 19 and 15 us against 72 and 30 us.
 template <typename T, int MODE, bool HAS_DOT>
 __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsSize& z, char* lds) {
     const RowsLds at = rows_lds<T>(z);
