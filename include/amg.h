@@ -218,6 +218,11 @@ amg_status amg_pcg_solve_noalloc(amg_hierarchy* h, const double* b, double* x, d
  * (the new coarsest operator is not positive definite; the hierarchy must
  * then be freed), HIP.
  * Not to be called while a solve on the same hierarchy is running.
+ * amg_vcycle and amg_level_spmv that the caller recorded in a graph before the
+ * update read the new values when the graph is replayed, with the smoother
+ * coefficients (CHEBYSHEV, JACOBI_SCALED) of the time they were recorded; recorded
+ * anew they have the present ones, and are faster where rows have begun or ceased
+ * to repeat.
  */
 amg_status amg_update_values(amg_hierarchy* h, const double* val, amg_ptr_kind kind, void* hip_stream);
 

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <utility>
 #include <vector>
@@ -236,11 +237,17 @@ struct DCsr {
     // (the next record holds their ends), then the windows of columns it
     // gathers from: number, total length, and first column less
     // the group's first row, and length, of each, ascending (number 0: none).
+    // A launch that a caller recorded reads these buffers when it is replayed, so
+    // they stay where they are until the hierarchy is freed: an update writes into
+    // them, and where they are too small, into new ones, the old kept aside
+    // (dold).  A group whose record holds no rows, or more than the launch has LDS
+    // for, is read from val and col (rowptr, col and val never move).
     DBuf<uint16_t> drow_of;
     DBuf<int> doff, drun;
     DBuf<uint32_t> dinfo;
     DBuf<double> dval;
     DBuf<float> dval32;
+    std::vector<std::shared_ptr<void>> dold;
     int dk = 0;               // row blocks per group; 0: no dictionaries
     int64_t dn = 0, de = 0;   // dictionary rows and entries of all groups
     int dmax_n = 0, dmax_e = 0, dmax_x = 0;  // of the largest group; longest windows

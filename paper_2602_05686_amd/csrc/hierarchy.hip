@@ -434,7 +434,7 @@ void cast_fp32(Hierarchy& h, hipStream_t s) {
         if (!L.A.val32) L.A.val32.alloc((size_t)(L.A.nnz > 0 ? L.A.nnz : 1), mc);
         cast_vec<double, float>(L.A.nnz, L.A.val.get(), L.A.val32.get(), s);
         if (L.A.dk > 0) {
-            if (!L.A.dval32) L.A.dval32.alloc((size_t)L.A.de, mc);
+            if (!L.A.dval32) L.A.dval32.alloc(L.A.dval.size(), mc);
             cast_vec<double, float>(L.A.de, L.A.dval.get(), L.A.dval32.get(), s);
         }
         if (!L.dinv32) L.dinv32.alloc(nl, mc);

@@ -249,12 +249,6 @@ __global__ __launch_bounds__(kBlock) void k_rows_fill(int nblk, int dk, const in
 void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s) {
     A.dk = 0;
     A.dn = A.de = 0;
-    A.drow_of.release();
-    A.drun.release();
-    A.dinfo.release();
-    A.doff.release();
-    A.dval.release();
-    A.dval32.release();
     // one thread per row adds its entries in order, as the streaming kernel
     // does for rows up to kWideRow of a one-thread-per-row matrix
     if (A.group != 1 || A.max_len > kWideRow || A.n <= 0 || A.nnz <= 0) return;
@@ -267,7 +261,7 @@ void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s) {
     DBuf<int> cnt_n((size_t)groups, mc), cnt_e((size_t)groups, mc), first((size_t)A.n, mc),
         tmp(scan_tmp_size(groups), mc), result(R_WORDS + 2, mc);
     DBuf<uint32_t> record((size_t)A.n, mc);
-    A.drow_of.alloc((size_t)A.n, mc);
+    if (!A.drow_of) A.drow_of.alloc((size_t)A.n, mc);
     DBuf<int> drow((size_t)groups + 1, mc), dent((size_t)groups + 1, mc);
     zero_async(result.get(), R_WORDS * sizeof(int), s);
     hipLaunchKernelGGL(k_rows_count, dim3(groups), dim3(kBlock), 0, s, A.nblk, dk, (const int*)A.blk.get(),
@@ -281,14 +275,39 @@ void row_dictionaries(DCsr& A, MemCounter* mc, hipStream_t s) {
     int res[R_WORDS + 2];
     d2h(res, result.get(), R_WORDS + 2, s);
     const int64_t dn = res[R_WORDS], de = res[R_WORDS + 1];
+    // no rows in any record: what was recorded with dictionaries reads val and col
+    auto empty = [&] { zero_async(A.drun.get(), A.drun.size() * sizeof(int), s); };
     if (res[R_FAIL] || de * kDictShare > A.nnz) {
-        A.drow_of.release();
+        if (A.drun) empty();
+        else A.drow_of.release();
         return;
     }
-    A.dinfo.alloc((size_t)dn, mc);
-    A.doff.alloc((size_t)de, mc);
-    A.dval.alloc((size_t)de, mc);
-    A.drun.alloc((size_t)(groups + 1) * kDictRunWords, mc);
+    if (!A.drun || (size_t)dn > A.dinfo.size() || (size_t)de > A.doff.size()) {
+        // half as large again, so that all of them are a few times the largest
+        const size_t rows = std::max((size_t)dn, A.dinfo.size() * 3 / 2),
+                     entries = std::max((size_t)de, A.doff.size() * 3 / 2);
+        if (A.drun) {
+            empty();
+            DBuf<uint16_t> row_of((size_t)A.n, mc);
+            MATAMG_HIP(hipMemcpyAsync(row_of.get(), A.drow_of.get(), sizeof(uint16_t) * (size_t)A.n,
+                                      hipMemcpyDeviceToDevice, s));
+            auto aside = [&](auto& b) {
+                using B = std::decay_t<decltype(b)>;
+                if (b) A.dold.push_back(std::make_shared<B>(std::move(b)));
+            };
+            aside(A.drow_of);
+            aside(A.drun);
+            aside(A.dinfo);
+            aside(A.doff);
+            aside(A.dval);
+            aside(A.dval32);
+            A.drow_of = std::move(row_of);
+        }
+        A.dinfo.alloc(rows, mc);
+        A.doff.alloc(entries, mc);
+        A.dval.alloc(entries, mc);
+        A.drun.alloc((size_t)(groups + 1) * kDictRunWords, mc);
+    }
     hipLaunchKernelGGL(k_rows_fill, dim3(groups), dim3(kBlock), 0, s, A.nblk, dk, (const int*)A.blk.get(),
                        (const int*)A.rowptr.get(), (const int*)A.col.get(), (const double*)A.val.get(),
                        (const int*)drow.get(), (const int*)dent.get(), (const int*)first.get(),

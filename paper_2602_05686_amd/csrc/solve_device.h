@@ -52,7 +52,8 @@ struct SArgs {
     const double* dotvec;  // SMOOTH: fused dot partner
     T c1, c2;
     DotTarget dt;
-    // row dictionaries (dk > 0: val, col, ... above are not read)
+    // row dictionaries (dk > 0: of the above, rowptr, col and val are read only for
+    // groups that have none)
     int dk, nblk;
     const uint16_t* drow_of;
     const uint32_t* dinfo;
@@ -599,6 +600,49 @@ __device__ __forceinline__ T row_sum(const T* lv, int k0, int len, X x) {
     return s;
 }
 
+// the dot terms of row blocks [b0, b1) of a group from row r0 on, in the streaming
+// kernel's order
+template <typename T>
+__device__ __forceinline__ void rows_dots(const SArgs<T>& a, int b0, int b1, int r0, const double* ld) {
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int b = b0 + (int)(threadIdx.x >> 6); b < b1; b += kBlock / 64) {
+        const int f = a.blk[b], n = a.blk[b + 1] - f;
+        double u = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) {
+            const int i = 64 * w + lane;
+            const double t = wave_sum(i < n ? ld[f - r0 + i] : 0.0);
+            u = w == 0 ? t : u + t;
+        }
+        if (lane == 0) a.dt.partial[b] = u;
+    }
+}
+
+// The rows of a group without a dictionary, one thread a row in the streaming
+// kernel's order of additions: only launches that were recorded before an update come
+// here (product of the 128^3 stack 31 us with dictionaries, 319 us here, launched
+// anew 104 us).  A thread's loads wait for one another, six entries at a time: as
+// many as leave the registers at what the groups with dictionaries need (one at a
+// time 1823 us; nine cost those a sixth of their wavefronts).
+template <typename T, int MODE, bool HAS_DOT>
+__device__ __forceinline__ void rows_plain(const SArgs<T>& a, int b0, int b1, T scale, double* ld) {
+    const int r0 = a.blk[b0], r1 = a.blk[b1];
+    __syncthreads();  // (every thread has read the scale's sums)
+    for (int r = r0 + (int)threadIdx.x; r < r1; r += kBlock) {
+        const RowOperands<T> o = row_operands<T, MODE>(a, r);
+        T s = 0;
+        int k = a.rowptr[r];
+        const int end = a.rowptr[r + 1];
+        auto x = [&](int e) { return operand<MODE>(a.x[a.col[e]], scale); };
+        row_chunk<6>(s, a.val, k, end, x);
+        row_chunk<3>(s, a.val, k, end, x);
+        row_chunk<1>(s, a.val, k, end, x);
+        const DotTerm dp = epilogue<T, MODE, HAS_DOT>(a, r, s, o);
+        if constexpr (HAS_DOT) ld[r - r0] = dp.a * dp.b;
+    }
+    if constexpr (HAS_DOT) rows_dots(a, b0, b1, r0, ld);
+}
+
 // Rows of group `g` (dk row blocks) from its dictionary in LDS, one thread
 // per row.  With max_x the operands come from LDS too: the rows of a group
 // gather from a few windows of consecutive columns (three planes of a mesh,
@@ -626,7 +670,8 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
     const int* rec = a.drun + (size_t)g * kDictRunWords;
     const int m0 = rec[0], m1 = rec[kDictRunWords], e0 = rec[1], e1 = rec[kDictRunWords + 1];
     const int* run = rec + 2;
-    const int nrun = z.max_x > 0 ? run[0] : 0, total = run[1];
+    const int total = run[1];
+    const int nrun = total <= z.max_x ? run[0] : 0;
     const T scale = operand_scale<T, MODE>(a, lds);
     const int first = r0 + (int)threadIdx.x;
     // the first row's record number and operands travel with the dictionary
@@ -635,6 +680,11 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
     if (first < r1) {
         id = a.drow_of[first];
         o = row_operands<T, MODE>(a, first);
+    }
+    // a launch recorded before an update may find none, or more than it has room for
+    if (m1 <= m0 || m1 - m0 > z.max_n || e1 - e0 > z.max_e) {
+        rows_plain<T, MODE, HAS_DOT>(a, b0, b1, scale, ld);
+        return;
     }
     if (nrun > 0) {
         // window j covers the columns first[j] on, at the places end[j - 1] on
@@ -691,20 +741,7 @@ __device__ __forceinline__ void rows_group(const SArgs<T>& a, int g, const RowsS
         const DotTerm dp = epilogue<T, MODE, HAS_DOT>(a, r, s, o);
         if constexpr (HAS_DOT) ld[r - r0] = dp.a * dp.b;
     }
-    if constexpr (HAS_DOT) {
-        __syncthreads();
-        const int lane = threadIdx.x & 63;
-        for (int b = b0 + (int)(threadIdx.x >> 6); b < b1; b += kBlock / 64) {
-            const int f = a.blk[b], n = a.blk[b + 1] - f;
-            double u = 0.0;
-            for (int w = 0; w < kBlock / 64; ++w) {
-                const int i = 64 * w + lane;
-                const double t = wave_sum(i < n ? ld[f - r0 + i] : 0.0);
-                u = w == 0 ? t : u + t;
-            }
-            if (lane == 0) a.dt.partial[b] = u;
-        }
-    }
+    if constexpr (HAS_DOT) rows_dots(a, b0, b1, r0, ld);
 }
 
 // The sizes of M's groups for a launch in precision T over `rows` rows of
