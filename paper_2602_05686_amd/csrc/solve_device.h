@@ -649,9 +649,9 @@ __device__ __forceinline__ void rows_plain(const SArgs<T>& a, int b0, int b1, T 
 // say), read once.  A row block's dot terms are summed in the streaming
 // kernel's order (its rows over four wavefronts, each by the wavefront tree,
 // the four sums in order).  What bounds it where it gathers is the cache path: the
-// texture address units are busy 84% of the time (FP64, 96^3 cube) and 76% (FP32,
-// 128^3 stack).  Staged, no unit is (128^3 stack: vector units 52%, address units
-// 50%, LDS 45%, HBM at half the rate of a plain read): a workgroup's steps -- the
+// texture address units are busy 83% of the time (FP64, 96^3 cube) and 75% (FP32,
+// 128^3 stack).  Staged, no unit is (128^3 stack: vector units 51%, address units
+// 50%, LDS 44%, HBM at half the rate of a plain read): a workgroup's steps -- the
 // windows, the barrier, the sums -- follow one another, and a CU's LDS has room
 // for six workgroups to fill the gaps.  The FP64 fine smoother of the 128^3 stack
 // takes 33 us for the 103 MB of its vectors (staged; 41 us gathering), against 116
